@@ -595,100 +595,64 @@ __global__ void __launch_bounds__(64 * NW) k_finish(LayerArgs a) {
 }
 
 // ============================================================ large-M tile kernel
-// Block = 512 / WR waves over a 512 x TC tile; wave w owns rows [row0 + WR w, +WR) as WR / 32
-// fragments of 32 and all columns [m0, m0 + TC) as TC / 32 fragments of 32 (TC = 96 or 128): a
-// WR x TC accumulator (in the accumulation registers) on 32x32x32 sparse MFMA. Each dequantised
-// weight fragment feeds TC / 32 MFMAs and no weight row is dequantised by two waves; the wider
-// tile spends less dequantisation per MFMA, the narrower one gives more tiles to even out the
-// last round of blocks (the plan picks per shape). WR = 64 (the launched form) runs two waves per
-// SIMD (8 waves, 64 x TC accumulators each), so that one wave's dequantisation, LDS reads and
-// waits overlap the other's MFMAs, at twice the B-fragment reads from LDS; WR = 128 runs one (4
-// waves, 128 x TC accumulators).
+// Block = 8 waves over a 512 x TC tile; wave w owns rows [row0 + 64 w, + 64) as two fragments of 32 and
+// all columns [m0, m0 + TC) as TC / 32 fragments of 32 (TC = 96 or 128): a 64 x TC accumulator on
+// 32x32x32 sparse MFMA, two waves per SIMD. Each dequantised weight fragment feeds TC / 32 MFMAs and no
+// weight row is dequantised by two waves; the wider tile spends less dequantisation per MFMA, the
+// narrower one gives more tiles to even out the last round of blocks (the plan picks per shape).
 // Per 128-wide reduction chunk, the tile's packed words (codes, index words and scales of its
 // 512 rows, in four 128-row groups) and the fp16 activation tile [TC x 128] go straight from
 // memory to LDS (direct loads), so no register holds data still in flight: the words into a ring of three stages, two
 // chunks ahead; the activations into a ring of three stages, two chunks ahead, at TC = 96, or of
-// two stages, one chunk ahead, at TC = 128 (three would not fit in LDS next to the words). A
-// chunk's words are read from LDS, and its first step dequantised, during the last step of the
-// chunk before. Activation rows in LDS are 256 B with the 16-byte column index XOR-swizzled by
+// two stages, one chunk ahead, at TC = 128 (three would not fit in LDS next to the words).
+// Activation rows in LDS are 256 B with the 16-byte column index XOR-swizzled by
 // the row, so B-fragment reads (32 rows at one column) hit distinct banks. The backward also
 // brings each 128-row group's scale row into LDS with the activations.
 // Each wave loads the words of its own rows; the scales (and in the backward the scale row) of a
-// 128-row group are loaded by every wave of the group, so that all waves issue the same loads
-// (two waves then write the same bytes).
+// 128-row group are loaded by both waves of the group (the same bytes), so that all waves issue
+// the same loads and a wave reads only words it loaded itself.
+// LDS reads are written out (ds_read with immediate offsets, explicit waits that name the registers
+// they complete). Left to the compiler, most fragments were read right before their MFMAs, each
+// wait the whole LDS latency, and one wait per chunk drained every direct load in flight: the loop
+// took about 3600 cycles per chunk of TC = 128 against 2048 of MFMA issue (prefill 11008 x 4096, M 2048:
+// 138 -> 132 us; 70B forward at M 8192: 2172 -> 2090 us).
 constexpr int kTR = 512;
-template <int TC, int WR> struct TileShape {
-  static constexpr int kWaves = kTR / WR;              // waves per block
-  static constexpr int kThreads = 64 * kWaves;
-  static constexpr int kFn = WR / 32;                  // row fragments per wave
+constexpr int kTWaves = 8, kTThreads = 64 * kTWaves;
+template <bool BWD, int TC> struct TileShape {
+  static constexpr int kFn = 2;                        // row fragments per wave
   static constexpr int kFm = TC / 32;                  // column fragments per wave
-  static constexpr int kActRows = TC / kWaves;         // activation rows each wave brings in
+  static constexpr int kActRows = TC / kTWaves;        // activation rows each wave brings in
   static constexpr int kActLoads = kActRows / 4;       // ... four rows per direct load
   static constexpr int kStagesX = TC == 128 ? 2 : 3;   // activation stages
   static constexpr int kAhead = kStagesX - 1;          // chunks of activations in flight ahead
   static_assert(kActRows % 4 == 0, "whole direct loads of four rows");
+  // Direct loads per wave and chunk: words (two of codes, one of index words, in the forward one of
+  // scales) and activations (in the backward with one scale row). Chunk c issues chunk c + kAhead's
+  // activations in its first step and chunk c + 2's words in its second.
+  static constexpr int kWords = BWD ? 3 : 4;
+  static constexpr int kAct = kActLoads + (BWD ? 1 : 0);
+  // LDS: activations [stage][TC][256 B], words [stage]: codes [group][fragment][lane][16 B], index words
+  // [group][row][16 B], scales [group][row] fp16 (forward); backward scale rows [stage][group][four
+  // copies of 256 B]
+  static constexpr uint32_t kX = TC * 256, kCodes = 16384, kMeta = 8192, kW = kCodes + kMeta + (BWD ? 0 : 1024);
+  static constexpr uint32_t kWBase = kStagesX * kX, kSBase = kWBase + 3 * kW, kBytes = kSBase + (BWD ? kStagesX * 4096 : 0);
 };
-// Direct loads per thread per chunk: activation loads (kActLoads, and in the backward one
-// scale-row load) and packed words (WR / 32 code loads, WR / 64 index word loads, and in the
-// forward 1 scale load).
-// kAhead 2: chunk c issues chunk c + 2's words in its first step and chunk c + 2's activations in
-// its second; kAhead 1: chunk c + 1's activations in its first step and chunk c + 2's words in its
-// second. The one barrier of chunk c opens its last step, after which the wave reads chunk c + 1's
-// words and first B fragments: there chunk c + 1 must have landed, so only the loads chunk c
-// issued for chunk c + 2 may still be outstanding (kTop). The prologue issues the loads of chunks
-// 0 and 1 in the same order and waits with the same count before a barrier of its own.
-template <bool BWD, int TC, int WR> struct TileCounts {
-  static constexpr bool kActFirst = TileShape<TC, WR>::kAhead == 1;
-  static constexpr int kWords = WR / 32 + WR / 64 + (BWD ? 0 : 1);
-  static constexpr int kAct = TileShape<TC, WR>::kActLoads + (BWD ? 1 : 0);
-  static constexpr int kTop = kActFirst ? kWords : kAct + kWords;
-};
-
-static_assert(vmcnt_wait(40) == 0x8F78u && vmcnt_wait(5) == 0x0F75u && TileCounts<true, 96, 64>::kTop < 64, "s_waitcnt encoding");
+static_assert(vmcnt_wait(40) == 0x8F78u && vmcnt_wait(5) == 0x0F75u, "s_waitcnt encoding");
 static_assert(vmcnt_lgkm0_wait(20) == 0x4074u, "s_waitcnt encoding");
 
+template <int I> using ic = std::integral_constant<int, I>;
+template <uint32_t I> using uc = std::integral_constant<uint32_t, I>;
 
-// One chunk's packed words of the tile's four 128-row groups, as the direct loads lay them down
-// (lane L of a load at 16 L, or 4 L for 2-byte loads): codes [group][fragment][lane] (16 B: the
-// lane's four code words), index words [group][row slot] (16 B: the row's four words; row slot =
-// 32 fragment + row in fragment), scales [group][row slot] (fp16 in the low half of a dword). Reads index these
-// arrays directly (no pointer casts, and no 8-byte reads the compiler would pair into one
-// instruction that has lost track of its address), so that the compiler can tell the stages
-// apart and does not wait for every direct load in flight.
-template <bool BWD>
-struct TileWordsLds {
-  u32x4_t cw[4][4][64];
-  u32x4_t mw[4][128];
-  uint16_t sw[BWD ? 1 : 4][BWD ? 2 : 128];
-};
-// one chunk's packed words of one lane (FN row fragments), read from LDS
-template <int FN>
-struct TileWords {
-  u32x4_t cw[FN];
-  u32x2_t mw[FN];
-  uint32_t sw[FN];
-};
-
-template <bool BWD, int TC, int WR>
+template <bool BWD, int TC>
 SLIM_DEV void tile_body(const LayerArgs& a) {
-  using Sh = TileShape<TC, WR>;
-  using Ct = TileCounts<BWD, TC, WR>;
+  using Sh = TileShape<BWD, TC>;
   constexpr int kTC = TC, kFn = Sh::kFn, kFm = Sh::kFm, kStagesX = Sh::kStagesX;
-  // one array per stage (the stages of chunk c are c % 3 for the words and c % kStagesX for the
-  // activations, constants in the loop unrolled by six), so that reads of one stage are not
-  // ordered behind loads still landing in another
-  __shared__ __attribute__((aligned(16))) _Float16 xs0[kTC][128], xs1[kTC][128], xs2[kStagesX == 3 ? kTC : 1][128];
-  __shared__ __attribute__((aligned(16))) TileWordsLds<BWD> ws0, ws1, ws2;
-  __shared__ __attribute__((aligned(16))) _Float16 ss0[BWD ? 4 : 1][512], ss1[BWD ? 4 : 1][512],
-      ss2[BWD && kStagesX == 3 ? 4 : 1][512];
-  auto xs_at = [&](int stg) -> _Float16(*)[128] { return stg == 0 ? xs0 : (stg == 1 ? xs1 : xs2); };
-  auto ws_at = [&](int stg) -> TileWordsLds<BWD>& { return stg == 0 ? ws0 : (stg == 1 ? ws1 : ws2); };
-  auto ss_at = [&](int stg) -> _Float16(*)[512] { return stg == 0 ? ss0 : (stg == 1 ? ss1 : ss2); };
+  __shared__ __attribute__((aligned(16))) uint8_t lds[Sh::kBytes];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int ha = lane >> 5;
+  const int ha = lane >> 5, l32 = lane & 31;
   // the wave's 128-row group and its first fragment there
-  const int grp = WR == 128 ? wave : wave >> 1, fbase = WR == 128 ? 0 : 2 * (wave & 1);
+  const int grp = wave >> 1, fbase = 2 * (wave & 1);
   // XCD-aware tile order: block b runs on XCD b % 8 (workgroups are dealt round robin), and XCD x
   // takes positions [x Q, (x + 1) Q) of a tile order that walks bands of kb row tiles column
   // by column. The blocks an XCD runs together then cover a few row tiles x a few column tiles,
@@ -705,17 +669,16 @@ SLIM_DEV void tile_body(const LayerArgs& a) {
   const int64_t rb = R - band * kb < kb ? R - band * kb : kb;   // rows in this band
   const int64_t rt = band * kb + q % rb, ct = q / rb;
   const int64_t row0 = rt * kTR, m0 = ct * kTC;
-  const int64_t wrow0 = row0 + WR * wave;
+  const int64_t wrow0 = row0 + 64 * wave;
   const int64_t nch = a.red / 128;
 
-  // Addresses. Per-lane offsets are derived inside each chunk from a few base registers (made
-  // opaque per chunk) instead of being kept live across the loop. Rows past the matrix (or past
-  // M) get offsets at or beyond their resource's extent and read as zero; their results are not
-  // stored. The uniform chunk offset only ever moves a valid row within that row.
+  // Addresses. Rows past the matrix (or past M) get offsets at or beyond their resource's extent and
+  // read as zero; their results are not stored. The uniform chunk offset only ever moves a valid row
+  // within that row.
   // packed words: resources from the first 16-row block of the wave's 128-row group (clamped
   // into the matrix; rows is a multiple of 16). Relative to it, row d of chunk c sits in slot
   // ((d / 16) nch + c) 16 + d % 16; the chunk adds 16 slots, and 32 rows (two blocks) add
-  // 32 nch slots, fstep bytes of codes (32 B per slot) and, per 64 rows, of index words (16 B).
+  // 32 nch slots, fstep bytes of codes (32 B per slot).
   const int64_t grow0 = row0 + 128 * grp;
   const int64_t wblk = (grow0 < a.rows ? grow0 : a.rows - 16) / 16;
   const int64_t nblk = a.rows / 16 - wblk;
@@ -725,8 +688,8 @@ SLIM_DEV void tile_body(const LayerArgs& a) {
   const uint32_t d0 = (uint32_t)(grow0 - 16 * wblk) + 32u * (uint32_t)fbase, snch = 16u * (uint32_t)nch;
   auto rel_slot = [&](uint32_t d) { return (d >> 4) * snch + (d & 15u); };
   const uint32_t fstep = 1024u * (uint32_t)nch;
-  const uint32_t co0 = rel_slot(d0 + (uint32_t)(lane & 31)) * 32u + 16u * ha;   // codes: the wave's fragment 0
-  const uint32_t mo0 = rel_slot(d0 + (uint32_t)lane) * 16u;                     // index words: the wave's rows 0..63
+  const uint32_t co0 = rel_slot(d0 + (uint32_t)l32) * 32u + 16u * ha;           // codes: the wave's fragment 0
+  const uint32_t mo0 = rel_slot(d0 + (uint32_t)lane) * 16u;                     // index words: the wave's 64 rows
   const uint32_t so0 = rel_slot(d0 - 32u * (uint32_t)fbase + 2u * (uint32_t)lane) * 2u;   // scales: group rows 2 L, 2 L + 1
 
   // activation chunk c -> stage c % kStagesX: wave w writes rows R w .. R w + R - 1 (R = kActRows),
@@ -741,50 +704,98 @@ SLIM_DEV void tile_body(const LayerArgs& a) {
   const uint32_t xstep = 8u * (uint32_t)a.red;
   const rsrc_t rg = make_rsrc(a.scales + (16 * wblk / 128) * a.red, a.red * 2);   // backward: the group's scale row
 
-  auto dma_words = [&](int64_t c, int stg, uint32_t co, uint32_t mo, uint32_t so) {
+  // direct load i of a chunk's words (codes, codes, index words, scales) into stage z
+  auto dma_word = [&](int64_t c, int z, int i, uint32_t co, uint32_t mo, uint32_t so) {
     const int cc = (int)clamp_hi(c, nch - 1);
-    TileWordsLds<BWD>& W = ws_at(stg);
-#pragma unroll
-    for (int fn = 0; fn < kFn; ++fn)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rc, (lds_ptr_t)&W.cw[grp][fbase + fn][0], 16, co + fn * fstep, 512 * cc, 0, 0);
-#pragma unroll
-    for (int j = 0; j < kFn / 2; ++j)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rm, (lds_ptr_t)&W.mw[grp][32 * fbase + 64 * j], 16, mo + j * fstep, 256 * cc, 0, 0);
-    if (!BWD) __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_ptr_t)&W.sw[grp][0], 4, so, 32 * cc, 0, 0);
+    uint8_t* W = lds + Sh::kWBase + (uint32_t)z * Sh::kW;
+    if (i < 2)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rc, (lds_ptr_t)(W + 1024 * (4 * grp + fbase + i)), 16, co + i * fstep, 512 * cc, 0, 0);
+    else if (i == 2)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rm, (lds_ptr_t)(W + Sh::kCodes + 2048 * grp + 512 * fbase), 16, mo, 256 * cc, 0, 0);
+    else
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_ptr_t)(W + Sh::kCodes + Sh::kMeta + 256 * grp), 4, so, 32 * cc, 0, 0);
   };
-  auto dma_act = [&](int64_t c, int stg, uint32_t xo) {
+  // direct load i of a chunk's activations (the last one in the backward: the group's scale row
+  // s16[n, g] of this chunk, four copies) into stage z
+  auto dma_act = [&](int64_t c, int z, int i, uint32_t xo) {
     const int cc = (int)clamp_hi(c, nch - 1);
-#pragma unroll
-    for (int i = 0; i < Sh::kActLoads; ++i)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (lds_ptr_t)&xs_at(stg)[Sh::kActRows * wave + 4 * i][0], 16,
+    if (i < Sh::kActLoads)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (lds_ptr_t)(lds + (uint32_t)z * Sh::kX + (uint32_t)(Sh::kActRows * wave + 4 * i) * 256u), 16,
                                                (xo ^ (16u * ((uint32_t)(Sh::kActRows * wave + 4 * i) & 15u))) + (uint32_t)i * xstep,
                                                256 * cc, 0, 0);
-    if (BWD) {
-      // the group's scale row s16[n, g] for this chunk (g = the wave's 128-row group), four copies
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rg, (lds_ptr_t)&ss_at(stg)[grp][0], 16, 16u * lslot, 256 * cc, 0, 0);
-    }
+    else
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rg, (lds_ptr_t)(lds + Sh::kSBase + (uint32_t)z * 4096u + 1024u * (uint32_t)grp), 16,
+                                               16u * (uint32_t)lslot, 256 * cc, 0, 0);
   };
-  auto read_words = [&](int stg, TileWords<kFn>& t) {
-    const TileWordsLds<BWD>& W = ws_at(stg);
-#pragma unroll
-    for (int fn = 0; fn < kFn; ++fn) {
-      t.cw[fn] = W.cw[grp][fbase + fn][lane];
-      const u32x4_t m4 = W.mw[grp][32 * (fbase + fn) + (lane & 31)];
-      t.mw[fn] = ha ? u32x2_t{m4[2], m4[3]} : u32x2_t{m4[0], m4[1]};
-      t.sw[fn] = BWD ? 0u : W.sw[grp][32 * (fbase + fn) + (lane & 31)];
+
+  auto rd16 = [](uint32_t addr, auto oc) -> u32x4_t {
+    u32x4_t v;
+    asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(v) : "v"(addr), "i"(decltype(oc)::value));
+    return v;
+  };
+  auto rd8 = [](uint32_t addr, auto oc) -> u32x2_t {
+    u32x2_t v;
+    asm volatile("ds_read_b64 %0, %1 offset:%2" : "=v"(v) : "v"(addr), "i"(decltype(oc)::value));
+    return v;
+  };
+  auto rd2 = [](uint32_t addr, auto oc) -> uint32_t {
+    uint32_t v;
+    asm volatile("ds_read_u16 %0, %1 offset:%2" : "=v"(v) : "v"(addr), "i"(decltype(oc)::value));
+    return v;
+  };
+  const uint32_t lb = (uint32_t)(uintptr_t)(lds_ptr_t)lds;
+  // one chunk's packed words of one lane: per row fragment four code words, two index words, the scale
+  struct Words {
+    u32x4_t cw[kFn];
+    u32x2_t mw[kFn];
+    uint32_t sw[kFn];
+  };
+  const uint32_t cwo = lb + Sh::kWBase + 1024u * (uint32_t)(4 * grp + fbase) + 16u * (uint32_t)lane;
+  const uint32_t mwo = lb + Sh::kWBase + Sh::kCodes + 2048u * (uint32_t)grp + 16u * (uint32_t)(32 * fbase + l32) + 8u * (uint32_t)ha;
+  const uint32_t swo = lb + Sh::kWBase + Sh::kCodes + Sh::kMeta + 256u * (uint32_t)grp + 2u * (uint32_t)(32 * fbase + l32);
+  constexpr int kWordReads = BWD ? 4 : 6;
+  auto read_words = [&](auto zc, Words& t) {
+    constexpr uint32_t o = decltype(zc)::value * Sh::kW;
+    t.cw[0] = rd16(cwo, uc<o>{});
+    t.cw[1] = rd16(cwo, uc<o + 1024>{});
+    t.mw[0] = rd8(mwo, uc<o>{});
+    t.mw[1] = rd8(mwo, uc<o + 512>{});
+    if constexpr (!BWD) {
+      t.sw[0] = rd2(swo, uc<o>{});
+      t.sw[1] = rd2(swo, uc<o + 64>{});
     }
   };
   const NibbleConsts nk = nibble_consts_reg();
-  auto dequant = [&](const TileWords<kFn>& t, int st, h8_t* av) {
-#pragma unroll
-    for (int fn = 0; fn < kFn; ++fn)
-      av[fn] = BWD ? dequant_word_int(t.cw[fn][st], nk) : dequant_word(t.cw[fn][st], splat_h2(t.sw[fn]), nk);
+  auto dequant = [&](const Words& t, int st, int fn) -> h8_t {
+    return BWD ? dequant_word_int(t.cw[fn][st], nk) : dequant_word(t.cw[fn][st], splat_h2(t.sw[fn]), nk);
   };
-  // B-fragment reads: fragment fm of step st reads row 32 fm + L % 32 at 16-byte column slots
-  // (2 st + L / 32) ^ (L % 16) (low half) and that + 8 (high half); with
-  // bo = 256 (L % 32) + 16 ((L % 16) ^ (L / 32)) these are at bytes 8192 fm + (bo ^ 32 st) and
-  // 8192 fm + (bo ^ (32 st + 128)) of the stage.
-  const uint32_t bo0 = 256u * (uint32_t)(lane & 31) + 16u * (uint32_t)((lane & 15) ^ ha);
+  // B fragment fm of step st: row 32 fm + L % 32 at 16-byte column slots (2 st + L / 32) ^ (L % 16) (low half)
+  // and that ^ 8 (high half): with bo = 256 (L % 32) + 16 ((L % 16) ^ (L / 32)) at bytes
+  // 8192 fm + (bo ^ 32 st) and 8192 fm + (bo ^ (32 st + 128)) of the stage; the third stage of 24 KiB lies
+  // past the 16-bit offset of a DS instruction and gets its addresses by an addition
+  const uint32_t bo0 = 256u * (uint32_t)l32 + 16u * (uint32_t)((lane & 15) ^ ha);
+  const uint32_t gso = lb + Sh::kSBase + 1024u * (uint32_t)grp + 16u * (uint32_t)ha;    // backward: the scale row
+  struct Bfrag {
+    u32x4_t lo, hi;
+  };
+  Bfrag bq[kFm];
+  struct Scl {
+    u32x4_t lo, hi;
+  };
+  Scl sq[BWD ? 2 : 1];
+  Bfrag bx;
+  auto read_b = [&](auto zc, auto stc, auto fmc, uint32_t bo, Bfrag& F) {
+    constexpr uint32_t z = decltype(zc)::value, st = decltype(stc)::value, fm = decltype(fmc)::value;
+    constexpr bool far = z == 2;
+    const uint32_t alo = lb + (bo ^ (32u * st)) + (far ? 2 * Sh::kX : 0u), ahi = lb + (bo ^ (32u * st + 128u)) + (far ? 2 * Sh::kX : 0u);
+    F.lo = rd16(alo, uc<(far ? 0 : z * Sh::kX) + 8192 * fm>{});
+    F.hi = rd16(ahi, uc<(far ? 0 : z * Sh::kX) + 8192 * fm>{});
+  };
+  auto read_s = [&](auto zc, auto stc, Scl& s) {
+    constexpr uint32_t o = decltype(zc)::value * 4096 + 32 * decltype(stc)::value;
+    s.lo = rd16(gso, uc<o>{});
+    s.hi = rd16(gso, uc<o + 128>{});
+  };
 
   f16_t acc[kFn][kFm];
 #pragma unroll
@@ -793,123 +804,162 @@ SLIM_DEV void tile_body(const LayerArgs& a) {
     for (int fm = 0; fm < kFm; ++fm)
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[fn][fm][v] = 0.f;
-
-  // words of chunk c in set c % 3 (read during chunk c - 1); A operands double-buffered by step
-  TileWords<kFn> tw[3];
+  Words tw[2];
+  if (BWD) tw[0].sw[0] = tw[0].sw[1] = tw[1].sw[0] = tw[1].sw[1] = 0u;
   h8_t aq[2][kFn];
-  // B fragment fm of step st from activation stage xstg
-  auto read_b = [&](int xstg, int st, int fm, uint32_t bo, h16_t& bv) {
-    const char* xsb = reinterpret_cast<const char*>(&xs_at(xstg)[0][0]);
-    h8_t lo = *reinterpret_cast<const h8_t*>(xsb + (bo ^ (32u * st)) + 8192 * fm);
-    h8_t hi = *reinterpret_cast<const h8_t*>(xsb + (bo ^ (32u * st + 128u)) + 8192 * fm);
-    if (BWD) {
-      const int c16 = 2 * st + ha;
-      lo = mul_h8(lo, *reinterpret_cast<const h8_t*>(&ss_at(xstg)[grp][8 * c16]));
-      hi = mul_h8(hi, *reinterpret_cast<const h8_t*>(&ss_at(xstg)[grp][8 * c16 + 64]));
-    }
-    bv = cat16(lo, hi);
-  };
-  // one B buffer, refilled fragment by fragment (below)
-  h16_t bq[kFm];
 
-  dma_words(0, 0, co0, mo0, so0);
-  dma_act(0, 0, xo0);
-  dma_words(1, 1, co0, mo0, so0);
-  if (!Ct::kActFirst) dma_act(1, 1, xo0);
-  // chunk 0 has landed once only chunk 1's loads are outstanding; the other waves brought in
-  // part of it. The barrier is issued as a bare instruction: the builtin would also make this
-  // wave wait for every direct-to-LDS load in flight, including the ones for the next chunk.
-  __builtin_amdgcn_s_waitcnt(vmcnt_lgkm0_wait(Ct::kTop));
-  asm volatile("s_barrier" ::: "memory");
-  read_words(0, tw[0]);
-  dequant(tw[0], 0, aq[0]);
 #pragma unroll
-  for (int fm = 0; fm < kFm; ++fm) read_b(0, 0, fm, bo0, bq[fm]);
+  for (int i = 0; i < Sh::kAct; ++i) dma_act(0, 0, i, xo0);
+#pragma unroll
+  for (int i = 0; i < Sh::kWords; ++i) dma_word(0, 0, i, co0, mo0, so0);
+  if (Sh::kAhead == 2)
+#pragma unroll
+    for (int i = 0; i < Sh::kAct; ++i) dma_act(1, 1, i, xo0);
+#pragma unroll
+  for (int i = 0; i < Sh::kWords; ++i) dma_word(1, 1, i, co0, mo0, so0);
+  // chunk 0 has landed once only chunk 1's loads are outstanding; the other waves brought in part of its
+  // activations. The barriers are bare instructions: the builtin would also make this wave wait for every
+  // direct load in flight.
+  __builtin_amdgcn_s_waitcnt(vmcnt_lgkm0_wait(Sh::kWords + (Sh::kAhead == 2 ? Sh::kAct : 0)));
+  asm volatile("s_barrier" ::: "memory");
+  read_words(ic<0>{}, tw[0]);
+  asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(tw[0].cw[0]), "+v"(tw[0].cw[1]), "+v"(tw[0].mw[0]), "+v"(tw[0].mw[1]), "+v"(tw[0].sw[0]), "+v"(tw[0].sw[1]));
+#pragma unroll
+  for (int fn = 0; fn < kFn; ++fn) aq[0][fn] = dequant(tw[0], 0, fn);
+  if constexpr (BWD) read_s(ic<0>{}, ic<0>{}, sq[0]);
+  read_b(ic<0>{}, ic<0>{}, ic<0>{}, bo0, bq[0]);
+  read_b(ic<0>{}, ic<0>{}, ic<1>{}, bo0, bq[1]);
+  read_b(ic<0>{}, ic<0>{}, ic<2>{}, bo0, bq[2]);
+  if constexpr (kFm == 4) read_b(ic<0>{}, ic<0>{}, ic<3>{}, bo0, bq[3]);
+  auto landed = [&]() {
+    asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(bq[0].lo), "+v"(bq[0].hi), "+v"(bq[1].lo), "+v"(bq[1].hi), "+v"(bq[2].lo), "+v"(bq[2].hi));
+    if constexpr (kFm == 4) asm volatile("" : "+v"(bq[kFm - 1].lo), "+v"(bq[kFm - 1].hi));
+    if constexpr (BWD) asm volatile("" : "+v"(sq[0].lo), "+v"(sq[0].hi));
+  };
+  landed();
 
-  auto chunk = [&](int64_t c, auto zc, auto xc) {
-    constexpr int z = decltype(zc)::value;    // c % 3: word stage and register set
-    constexpr int stg = decltype(xc)::value;  // c % kStagesX: activation stage
-    // Nothing of the previous chunk is scheduled past this point.
-    __builtin_amdgcn_sched_barrier(0);
+  // Chunk c: activation stage xs, word stage z, word registers p. The MFMAs of a step run column fragment by
+  // column fragment; once the two of fragment fm have issued, its registers are refilled with the
+  // next step's fragment fm, so a read has kFm - 1 fragments' MFMAs to land (LDS reads return in order:
+  // before fragment fm's MFMAs, only the reads issued after its own may be outstanding). Beside them the next
+  // step's weights are dequantised and, in the first two steps, the direct loads go out, one after an
+  // MFMA (issued in a burst, the waves' loads would fill the address unit's queue and stall issue).
+  // The next chunk's words are this wave's own loads: the third step waits for the loads of chunk c - 1 and
+  // reads them. The chunk's one barrier sits inside the last step, after its first two fragments:
+  // there this wave's reads of chunk c's activation stage have returned and chunk c + 1's activations
+  // landed; the next chunk's first fragments are read from then on (the last of them into registers of
+  // their own) and waited for at the chunk's end, so that no read is in flight across the loop's edges,
+  // where the register allocator may move values.
+  auto chunk = [&](int64_t c, auto xc, auto zc, auto pc) {
+    constexpr int xs = decltype(xc)::value, z = decltype(zc)::value, p = decltype(pc)::value;
+    constexpr int xn = (xs + 1) % kStagesX, zn = (z + 1) % 3;
+    const Words& cur = tw[p];
+    Words& nxt = tw[p ^ 1];
     // this chunk's copies of the base offsets (opaque, so nothing derived from them is hoisted)
     uint32_t xo = xo0, co = co0, mo = mo0, so = so0, bo = bo0;
     asm volatile("" : "+v"(xo), "+v"(co), "+v"(mo), "+v"(so), "+v"(bo));
-    const TileWords<kFn>& cur = tw[z];
-    TileWords<kFn>& nxt = tw[(z + 1) % 3];
-    // Software pipeline over the four steps. The MFMAs of a step run column fragment by column
-    // fragment; once the kFn MFMAs of fragment fm have issued, its registers are refilled with
-    // the next step's fragment fm, while the next step's dequantised weights go to the other A
-    // buffer. The chunk's one barrier opens its last step: after it the next chunk's words are
-    // read and its first step dequantised, and its first B fragments are read during this step's
-    // MFMAs (step 0 of a chunk then starts without waiting on LDS).
+    auto step = [&](auto stc) {
+      constexpr int st = decltype(stc)::value;
+      // reads outstanding after a fragment's own, on arrival at its MFMAs
+      constexpr int kAfter = 2 * (kFm - 1);
+      auto frag = [&](auto fmc, auto barc) {
+        constexpr int fm = decltype(fmc)::value;
+        constexpr bool bar = decltype(barc)::value;
+        // the reads issued between: step 2's word reads (before its first fragment), the backward's scales
+        // of the next step (before its first fragment's refill); in the last step no refills before the barrier
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (bar) {
+          // the third fragment of the last step
+          asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(bq[2].lo), "+v"(bq[2].hi));
+          if constexpr (kFm == 4) asm volatile("" : "+v"(bq[kFm - 1].lo), "+v"(bq[kFm - 1].hi));
+          __builtin_amdgcn_s_waitcnt(vmcnt_wait(Sh::kAhead == 2 ? Sh::kAct + Sh::kWords : Sh::kWords));
+          asm volatile("s_barrier" ::: "memory");
+          if constexpr (BWD) read_s(ic<xn>{}, ic<0>{}, sq[0]);
+          read_b(ic<xn>{}, ic<0>{}, ic<0>{}, bo, bq[0]);
+          read_b(ic<xn>{}, ic<0>{}, ic<1>{}, bo, bq[1]);
+          read_b(ic<xn>{}, ic<0>{}, ic<kFm - 1>{}, bo, bx);
+          __builtin_amdgcn_sched_barrier(0);
+        } else if constexpr (st == 3) {
+          if constexpr (fm == 0) {
+            asm volatile("s_waitcnt lgkmcnt(%2)" : "+v"(bq[0].lo), "+v"(bq[0].hi) : "i"(kAfter));
+            // the next chunk's words, read before this fragment, landed with it (reads return in order)
+            asm volatile("" : "+v"(nxt.cw[0]), "+v"(nxt.cw[1]), "+v"(nxt.mw[0]), "+v"(nxt.mw[1]), "+v"(nxt.sw[0]), "+v"(nxt.sw[1]));
+          }
+          if constexpr (fm == 1) asm volatile("s_waitcnt lgkmcnt(%2)" : "+v"(bq[1].lo), "+v"(bq[1].hi) : "i"(kAfter - 2));
+          // fragment 3 landed at the barrier
+        } else {
+          constexpr int extra = (st == 2 ? kWordReads : 0) + (BWD && fm > 0 ? 2 : 0);
+          asm volatile("s_waitcnt lgkmcnt(%2)" : "+v"(bq[fm].lo), "+v"(bq[fm].hi) : "i"(kAfter + extra));
+        }
+        if constexpr (BWD) {
+          if constexpr (fm == 0) asm volatile("" : "+v"(sq[st & 1].lo), "+v"(sq[st & 1].hi));
+          bq[fm].lo = __builtin_bit_cast(u32x4_t, mul_h8(__builtin_bit_cast(h8_t, bq[fm].lo), __builtin_bit_cast(h8_t, sq[st & 1].lo)));
+          bq[fm].hi = __builtin_bit_cast(u32x4_t, mul_h8(__builtin_bit_cast(h8_t, bq[fm].hi), __builtin_bit_cast(h8_t, sq[st & 1].hi)));
+        }
+        const h16_t bv = cat16(__builtin_bit_cast(h8_t, bq[fm].lo), __builtin_bit_cast(h8_t, bq[fm].hi));
 #pragma unroll
-    for (int st = 0; st < 4; ++st) {
-      // direct loads into the stages read in chunk c - 1 (chunk c + kAhead's activations, chunk
-      // c + 2's words) during steps 0 and 1, one load after each MFMA (issued in a burst at the
-      // barrier, the waves' loads would fill the address unit's queue and stall issue)
-      if (st == (Ct::kActFirst ? 0 : 1)) dma_act(c + Sh::kAhead, (stg + Sh::kAhead) % kStagesX, xo);
-      if (st == (Ct::kActFirst ? 1 : 0)) dma_words(c + 2, (z + 2) % 3, co, mo, so);
-      if (st < 3) {
-        dequant(cur, st + 1, aq[(st + 1) & 1]);
+        for (int fn = 0; fn < kFn; ++fn) {
+          acc[fn][fm] = smfmac32(aq[st & 1][fn], bv, acc[fn][fm], (int)cur.mw[fn][st >> 1], st & 1);
+          const int i = kFn * fm + fn;
+          if constexpr (st == 0) {
+            if (i < Sh::kAct) dma_act(c + Sh::kAhead, (xs + Sh::kAhead) % kStagesX, i, xo);
+          }
+          if constexpr (st == 1) {
+            if (i < Sh::kWords) dma_word(c + 2, (z + 2) % 3, i, co, mo, so);
+          }
+          // the next step's weights: fragment 0 beside the first MFMAs, fragment 1 beside the middle ones
+          if (i == 1) aq[(st + 1) & 1][0] = dequant(st < 3 ? cur : nxt, (st + 1) & 3, 0);
+          if (i == 3) aq[(st + 1) & 1][1] = dequant(st < 3 ? cur : nxt, (st + 1) & 3, 1);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (st < 3) {
+          if constexpr (BWD && fm == 0) read_s(xc, ic<st + 1>{}, sq[(st + 1) & 1]);
+          read_b(xc, ic<st + 1>{}, fmc, bo, bq[fm]);
+        }
+      };
+      if constexpr (st == 2) {
+        // chunk c + 1's words were loaded in chunk c - 1: only chunk c's loads may be outstanding
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_waitcnt(vmcnt_wait(Sh::kAct + Sh::kWords));
+        read_words(ic<zn>{}, nxt);
+      }
+      if constexpr (st < 3) {
+        frag(ic<0>{}, std::false_type{});
+        frag(ic<1>{}, std::false_type{});
+        frag(ic<2>{}, std::false_type{});
+        if constexpr (kFm == 4) frag(ic<3>{}, std::false_type{});
       } else {
-        // chunk c + 1 has landed once only chunk c + 2's loads are outstanding, and this wave's
-        // reads of chunk c's activation stage (the last ones, for this step, were issued in the
-        // step before) have returned (lgkmcnt 0): after the barrier no wave reads that stage, and
-        // the next chunk's direct loads may refill it.
-        __builtin_amdgcn_sched_barrier(0);
-        __builtin_amdgcn_s_waitcnt(vmcnt_lgkm0_wait(Ct::kTop));
-        asm volatile("s_barrier" ::: "memory");
-        __builtin_amdgcn_sched_barrier(0);
-        read_words((z + 1) % 3, nxt);
-        dequant(nxt, 0, aq[0]);
+        frag(ic<0>{}, std::false_type{});
+        frag(ic<1>{}, std::false_type{});
+        frag(ic<2>{}, std::true_type{});
+        if constexpr (kFm == 4) {
+          read_b(ic<xn>{}, ic<0>{}, ic<2>{}, bo, bq[2]);
+          frag(ic<3>{}, std::false_type{});
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(bx.lo), "+v"(bx.hi));
+        bq[kFm - 1] = bx;
+        landed();
       }
-#pragma unroll
-      for (int fm = 0; fm < kFm; ++fm) {
-#pragma unroll
-        for (int fn = 0; fn < kFn; ++fn)
-          acc[fn][fm] = smfmac32(aq[st & 1][fn], bq[fm], acc[fn][fm], (int)cur.mw[fn][st >> 1], st & 1);
-        if (st < 3) read_b(stg, st + 1, fm, bo, bq[fm]);
-        else read_b((stg + 1) % kStagesX, 0, fm, bo, bq[fm]);
-      }
-      // interleave: each MFMA followed by a share of the VALU work and, in steps 0 and 1, by one
-      // direct load; the LDS reads of fragment fm follow its MFMAs (in the last step the next
-      // chunk's words are read first)
-      const int nvm = st == 0 ? (Ct::kActFirst ? Ct::kAct : Ct::kWords) : st == 1 ? (Ct::kActFirst ? Ct::kWords : Ct::kAct) : 0;
-#pragma unroll
-      for (int i = 0; i < kFn * kFm; ++i) {
-        if (st == 3 && i < 3 * kFn / 2) __builtin_amdgcn_sched_group_barrier(0x0100, 2, 0);   // DS read
-        __builtin_amdgcn_sched_group_barrier(0x0008, 1, 0);                          // MFMA
-        if (i < nvm) __builtin_amdgcn_sched_group_barrier(0x0020, 1, 0);             // VMEM read
-        __builtin_amdgcn_sched_group_barrier(0x0002, 4, 0);                          // VALU
-        if (i % kFn == kFn - 1) __builtin_amdgcn_sched_group_barrier(0x0100, 2, 0);   // DS read
-      }
-    }
+    };
+    step(ic<0>{});
+    step(ic<1>{});
+    step(ic<2>{});
+    step(ic<3>{});
   };
-  // full groups of six without guards (a load under a branch costs a full wait at the join),
-  // then at most five chunks
-  using I0 = std::integral_constant<int, 0>;
-  using I1 = std::integral_constant<int, 1>;
-  using I2 = std::integral_constant<int, 2>;
-  using X0 = std::integral_constant<int, 0>;
-  using X1 = std::integral_constant<int, 1>;
-  using X2 = std::integral_constant<int, kStagesX == 3 ? 2 : 0>;
-  using X3 = std::integral_constant<int, kStagesX == 3 ? 0 : 1>;
-  using X4 = std::integral_constant<int, kStagesX == 3 ? 1 : 0>;
-  using X5 = std::integral_constant<int, kStagesX == 3 ? 2 : 1>;
   int64_t c0 = 0;
   for (; c0 + 6 <= nch; c0 += 6) {
-    chunk(c0, I0{}, X0{});
-    chunk(c0 + 1, I1{}, X1{});
-    chunk(c0 + 2, I2{}, X2{});
-    chunk(c0 + 3, I0{}, X3{});
-    chunk(c0 + 4, I1{}, X4{});
-    chunk(c0 + 5, I2{}, X5{});
+    chunk(c0, ic<0>{}, ic<0>{}, ic<0>{});
+    chunk(c0 + 1, ic<1>{}, ic<1>{}, ic<1>{});
+    chunk(c0 + 2, ic<2 % kStagesX>{}, ic<2>{}, ic<0>{});
+    chunk(c0 + 3, ic<3 % kStagesX>{}, ic<0>{}, ic<1>{});
+    chunk(c0 + 4, ic<4 % kStagesX>{}, ic<1>{}, ic<0>{});
+    chunk(c0 + 5, ic<5 % kStagesX>{}, ic<2>{}, ic<1>{});
   }
-  if (c0 < nch) chunk(c0, I0{}, X0{});
-  if (c0 + 1 < nch) chunk(c0 + 1, I1{}, X1{});
-  if (c0 + 2 < nch) chunk(c0 + 2, I2{}, X2{});
-  if (c0 + 3 < nch) chunk(c0 + 3, I0{}, X3{});
-  if (c0 + 4 < nch) chunk(c0 + 4, I1{}, X4{});
+  if (c0 < nch) chunk(c0, ic<0>{}, ic<0>{}, ic<0>{});
+  if (c0 + 1 < nch) chunk(c0 + 1, ic<1>{}, ic<1>{}, ic<1>{});
+  if (c0 + 2 < nch) chunk(c0 + 2, ic<2 % kStagesX>{}, ic<2>{}, ic<0>{});
+  if (c0 + 3 < nch) chunk(c0 + 3, ic<3 % kStagesX>{}, ic<0>{}, ic<1>{});
+  if (c0 + 4 < nch) chunk(c0 + 4, ic<4 % kStagesX>{}, ic<1>{}, ic<0>{});
   // the ring's last loads (repeats of the final chunk) must land before the block's LDS is released
   __builtin_amdgcn_s_waitcnt(0);
 
@@ -931,10 +981,10 @@ SLIM_DEV void tile_body(const LayerArgs& a) {
 #pragma unroll
     for (int fn = 0; fn < kFn; ++fn) po[fn] = (uint32_t)((wrow0 + 32 * fn) / 32 * nj) * 1024u + lo16;
     // tm tiles of a group per wave: tile q = 8 fm + (step % 8) goes to byte 1024 q of the stage
-    constexpr int kTT = kFm * 8 / Sh::kWaves;
-    static_assert(kTT * Sh::kWaves == kFm * 8, "tm tiles of a group spread evenly over the waves");
+    constexpr int kTT = kFm * 8 / kTWaves;
+    static_assert(kTT * kTWaves == kFm * 8, "tm tiles of a group spread evenly over the waves");
     auto dma_t = [&](int64_t g, int stg) {
-      char* dst = reinterpret_cast<char*>(&xs_at(stg)[0][0]);
+      uint8_t* dst = lds + (uint32_t)stg * Sh::kX;
 #pragma unroll
       for (int i = 0; i < kTT; ++i) {
         // the tile row's offset per lane (rows past M lie beyond the resource's extent and read
@@ -942,7 +992,7 @@ SLIM_DEV void tile_body(const LayerArgs& a) {
         // that lane L of a fragment read needs (lo16) and lays them at 16 L, so the read of a
         // fragment is 1 KB in lane order (a read at lo16 would put lanes L and L + 8 of one
         // 16-lane pass in the same bank).
-        const int q = wave + Sh::kWaves * i, fm = q >> 3;
+        const int q = wave + kTWaves * i, fm = q >> 3;
         const int64_t t = clamp_hi(8 * g + (q & 7), nj - 1);
         const uint32_t vo = (uint32_t)((m0 + 32 * fm) / 32 * nj) * 1024u + lo16;
         __builtin_amdgcn_raw_ptr_buffer_load_lds(rt, (lds_ptr_t)(dst + 1024 * q), 16, vo, (int)(t * 1024), 0, 0);
@@ -965,9 +1015,26 @@ SLIM_DEV void tile_body(const LayerArgs& a) {
     // group 0 has landed once only the three steps of P loads issued after it are outstanding
     __builtin_amdgcn_s_waitcnt(vmcnt_wait(3 * kFn));
     asm volatile("s_barrier" ::: "memory");
-    // step t = 8 g + tt of group g (stage xstg); group g + 1 was issued at the group's start, after
-    // step g 8 + 2's P loads and before step 8 g + 3's
-    auto ad_step = [&](int64_t g, auto ttc, int xstg) {
+    // tm fragments of step tt of the group in stage xstg
+    h8_t tb[2][kFm];
+    auto read_t = [&](auto ttc, uint32_t ta, int set) {
+      constexpr uint32_t tt = decltype(ttc)::value;
+      u32x4_t v[kFm];
+      v[0] = rd16(ta, uc<1024 * tt>{});
+      v[1] = rd16(ta, uc<1024 * (8 + tt)>{});
+      v[2] = rd16(ta, uc<1024 * (16 + tt)>{});
+      if constexpr (kFm == 4) v[3] = rd16(ta, uc<1024 * (24 + tt)>{});
+#pragma unroll
+      for (int fm = 0; fm < kFm; ++fm) tb[set][fm] = __builtin_bit_cast(h8_t, v[fm]);
+    };
+    auto landed_t = [&](int set) {
+      asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(tb[set][0]), "+v"(tb[set][1]), "+v"(tb[set][2]));
+      if constexpr (kFm == 4) asm volatile("" : "+v"(tb[set][kFm - 1]));
+    };
+    // step t = 8 g + tt of group g (stage xstg): its tm fragments are in tb[tt % 2], the next step's are
+    // read beside its MFMAs; group g + 1 was issued at the group's start, after step 8 g + 2's P loads
+    // and before step 8 g + 3's
+    auto ad_step = [&](int64_t g, auto ttc, uint32_t ta) {
       constexpr int tt = decltype(ttc)::value;
       const int64_t t = 8 * g + tt;
       ad_load(t + 3, ar[(tt + 3) % 4]);
@@ -975,30 +1042,32 @@ SLIM_DEV void tile_body(const LayerArgs& a) {
       AdRegs& R = ar[tt % 4];
 #pragma unroll
       for (int fn = 0; fn < kFn; ++fn) asm volatile("" : "+v"(R.pa[fn]));
-      const char* src = reinterpret_cast<const char*>(&xs_at(xstg)[0][0]);
-      h8_t tb[kFm];
-#pragma unroll
-      for (int fm = 0; fm < kFm; ++fm) tb[fm] = *reinterpret_cast<const h8_t*>(src + 1024 * (8 * fm + tt) + 16 * lane);
+      if constexpr (tt < 7) read_t(ic<tt + 1>{}, ta, (tt + 1) & 1);
+      __builtin_amdgcn_sched_barrier(0);
       if (t < nj) {
 #pragma unroll
         for (int fn = 0; fn < kFn; ++fn)
 #pragma unroll
           for (int fm = 0; fm < kFm; ++fm)
-            acc[fn][fm] = mfma32(__builtin_bit_cast(h8_t, R.pa[fn]), tb[fm], acc[fn][fm]);
+            acc[fn][fm] = mfma32(__builtin_bit_cast(h8_t, R.pa[fn]), tb[tt & 1][fm], acc[fn][fm]);
       }
+      if constexpr (tt < 7) landed_t((tt + 1) & 1);
     };
     auto group = [&](int64_t g, int xstg) {
       // the next group into the next stage (read two or three groups ago, before the last
       // barrier); issued also after the last group, whose repeats land in a stage no wave reads
       dma_t(g + 1, (xstg + 1) % kStagesX);
-      ad_step(g, std::integral_constant<int, 0>{}, xstg);
-      ad_step(g, std::integral_constant<int, 1>{}, xstg);
-      ad_step(g, std::integral_constant<int, 2>{}, xstg);
-      ad_step(g, std::integral_constant<int, 3>{}, xstg);
-      ad_step(g, std::integral_constant<int, 4>{}, xstg);
-      ad_step(g, std::integral_constant<int, 5>{}, xstg);
-      ad_step(g, std::integral_constant<int, 6>{}, xstg);
-      ad_step(g, std::integral_constant<int, 7>{}, xstg);
+      const uint32_t ta = lb + (uint32_t)xstg * Sh::kX + 16u * (uint32_t)lane;
+      read_t(ic<0>{}, ta, 0);
+      landed_t(0);
+      ad_step(g, ic<0>{}, ta);
+      ad_step(g, ic<1>{}, ta);
+      ad_step(g, ic<2>{}, ta);
+      ad_step(g, ic<3>{}, ta);
+      ad_step(g, ic<4>{}, ta);
+      ad_step(g, ic<5>{}, ta);
+      ad_step(g, ic<6>{}, ta);
+      ad_step(g, ic<7>{}, ta);
       // this wave's reads of the stage have returned and the next group has landed (waited for
       // at step 3): after the barrier the stage may be refilled and the next group read
       __builtin_amdgcn_s_waitcnt(vmcnt_lgkm0_wait(3 * kFn));
@@ -1034,9 +1103,9 @@ SLIM_DEV void tile_body(const LayerArgs& a) {
   }
 }
 
-template <bool BWD, int TC, int WR>
-__global__ void __launch_bounds__(64 * (kTR / WR)) k_tile(LayerArgs a) {
-  tile_body<BWD, TC, WR>(a);
+template <bool BWD, int TC>
+__global__ void __launch_bounds__(kTThreads) k_tile(LayerArgs a) {
+  tile_body<BWD, TC>(a);
 }
 
 // Large-M activation preparation, one block per row m of act [M, red] (bf16 or fp16): the row's
@@ -1277,10 +1346,8 @@ int launch_layer(const LayerArgs& a, const SlimPlan& p, const uint16_t* act, int
   }
   SlimKernelTimer timer(BWD ? "tile_bwd" : "tile_fwd", s);
   dim3 grid((unsigned)(8 * ((p.sp_row_tiles * p.sp_col_tiles + 7) / 8)));
-  // 8 waves of 64 rows (the kernel also builds with 4 of 128, one wave per SIMD, which measured
-  // slower on every workload once tm came through LDS)
-  if (p.sp_cols_tile == 128) SLIM_LAUNCH(timer, (k_tile<BWD, 128, 64>), grid, dim3(TileShape<128, 64>::kThreads), s, a);
-  else SLIM_LAUNCH(timer, (k_tile<BWD, 96, 64>), grid, dim3(TileShape<96, 64>::kThreads), s, a);
+  if (p.sp_cols_tile == 128) SLIM_LAUNCH(timer, (k_tile<BWD, 128>), grid, dim3(kTThreads), s, a);
+  else SLIM_LAUNCH(timer, (k_tile<BWD, 96>), grid, dim3(kTThreads), s, a);
   return hipGetLastError() == hipSuccess ? SLIM_OK : SLIM_EDEVICE;
 }
 
