@@ -69,6 +69,7 @@ def parse():
 ROOT = os.path.dirname(os.path.abspath(__file__))
 KERNEL_SOURCES = ("include/slim.h", "paper_2608_24070_amd/csrc/api.cpp", "paper_2608_24070_amd/csrc/slim_host.h",
                   "paper_2608_24070_amd/csrc/slim_device.h", "paper_2608_24070_amd/csrc/sparse_gemm.hip",
+                  "paper_2608_24070_amd/csrc/mid_gemm.hip",
                   "paper_2608_24070_amd/csrc/adapter_gemm.hip", "paper_2608_24070_amd/csrc/pack.hip",
                   "paper_2608_24070_amd/csrc/train.hip", "paper_2608_24070_amd/csrc/quant.hip",
                   "paper_2608_24070_amd/csrc/lora.hip", "paper_2608_24070_amd/csrc/hybrid.hip")
@@ -174,9 +175,9 @@ def kernel_bytes(kernel, M, N, K, r, bwd, has_finish=True, qadapter=False):
     second = (rows * r // 2 + 2 * rows * ((r + 127) // 128)) if qadapter else 2 * r * rows
     if kernel.startswith("decode"):      # packed weight + adapter first factor + activations -> T (fp16)
         return weight + first + 2 * M * red + 2 * M * r + (0 if has_finish else 4 * M * rows)
-    if kernel.startswith("finish"):      # adapter second factor + T -> Y
+    if kernel.startswith(("finish", "mid_finish")):   # adapter second factor + T -> Y
         return second + 2 * M * r + 4 * M * rows
-    if kernel.startswith("tile"):        # packed weight + fp16 activations + second factor + T -> Y
+    if kernel.startswith(("tile", "mid_fwd", "mid_bwd")):   # packed weight + fp16 activations + second factor + T -> Y
         return weight + 2 * M * red + 2 * r * rows + 2 * M * r + 4 * M * rows
     if kernel.startswith("adapter_gemm"):  # fp16 activations + first factor -> T
         return 2 * M * red + 2 * r * red + 2 * M * r

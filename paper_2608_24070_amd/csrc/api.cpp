@@ -55,7 +55,69 @@ int slim_check_pack_bwd(const void* codes, const void* meta, const void* scales,
   return SLIM_OK;
 }
 
-int slim_make_plan(bool bwd, int64_t M, int64_t N, int64_t K, int64_t r, SlimPlan* p) {
+namespace {
+
+// Slices of the adapter's first product in units of 128 ranks x 64 or 128 rows (at of them): as many as give
+// about one block per CU, a power of two up to eight (the last unit of a tile sums four at a time) of at
+// least 512 positions.
+int64_t adapter_slices(int64_t at, int64_t red) {
+  int64_t s = 8;
+  while (s > 1 && (at * s > 256 || red < 512 * s)) s /= 2;
+  return s;
+}
+
+// The middle path, where 512-row tiles are too few for the chip: 128 x 64 tiles, two blocks per CU, or
+// 256 x 128, one, over S slices of the reduction, whichever the cost below favours. Returns false where the
+// 512-row tiles are the better choice.
+bool mid_plan(bool bwd, int64_t M, int64_t rows, int64_t red, int64_t r, SlimPlan* q) {
+  const int64_t nch = red / 128, big = cdiv(rows, 256) * cdiv(M, 128);
+  // With about as many 256 x 128 tiles as CUs the 512-row tiles win (half the LDS and direct-load bytes per
+  // weight row; with an adapter also no fp32 partials through memory). Forward with an adapter: 11008 x
+  // 4096, M 512 (172 tiles) 69 against 76 us, M 700 (258) 90 against 79, 4096 x 4096, M 1500 (192) 84
+  // against 83; longer reductions pay for the partials longer (28672 x 8192, M 200 (224) 116 against 124).
+  // Backward with an adapter: 5120 x 13824, M 333 (162) 94 against 101, M 512 (216) 111 against 107, 4096 x
+  // 4096, M 1500 (192) 100 against 91. Without an adapter one whole round is still better in the forward
+  // (4096 x 4096, M 2048: 53 against 57), not in the backward, which scales every operand fragment (65
+  // against 64; M 1500: 56 against 60).
+  const int64_t limit = r == 0 ? (bwd ? 224 : 256) : (bwd ? 164 : (red >= 8192 ? 224 : 180));
+  if (big > limit) return false;
+  if (r > 0 && cdiv(M, 64) * cdiv(r, 128) > (int64_t)kCounterSlots) return false;
+  double best = 0;
+  for (int tc = 64; tc <= 128; tc += 64) {
+    const int64_t R = cdiv(rows, 2 * tc), C = cdiv(M, tc);
+    for (int64_t s = 1; s <= 8 && (s == 1 || nch >= 4 * s); ++s) {
+      const int64_t per = cdiv(nch, s), split = cdiv(nch, per), blocks = R * C * split;
+      // the partials, beside the fp16 activations, stay within the no-allocation entry point's scratch
+      if (s > 1 && split * R * C * 2 * tc * tc * 4 + 2 * M * red > (int64_t)SLIM_NOALLOC_SCRATCH_BYTES - (8 << 20)) break;
+      // microseconds per chunk: a lone 128 x 64 block on a CU 0.40, two 0.75, a 256 x 128 block 1.15;
+      // the adapter's chain beside them takes at least about 7
+      double t = per * (tc == 64 ? (blocks <= 256 ? 0.40 : 0.75 * cdiv(blocks, 512)) : 1.15 * cdiv(blocks, 256));
+      if (r > 0 && t < 7) t = 7;
+      // partials written and read at about 4 TB/s
+      if (split > 1 || r > 0) t += split * M * rows * 8 / 4e6;
+      if (best == 0 || t < best) {
+        best = t;
+        q->sp_cols_tile = tc;
+        q->sp_split = (int)split;
+        q->sp_chunks_per_split = per;
+      }
+    }
+  }
+  q->mid = true;
+  q->sp_rows_tile = 2 * q->sp_cols_tile;
+  q->sp_row_tiles = cdiv(rows, q->sp_rows_tile);
+  q->sp_col_tiles = cdiv(M, q->sp_cols_tile);
+  if (r > 0) {
+    q->ad_tiles_m = (int)cdiv(M, q->sp_cols_tile);
+    q->ad_tiles_j = (int)cdiv(r, 128);
+    q->ad_slice = cdiv(cdiv(red, adapter_slices((int64_t)q->ad_tiles_m * q->ad_tiles_j, red)), 64) * 64;
+    q->ad_split = (int)cdiv(red, q->ad_slice);
+  }
+  return true;
+}
+
+// `fewest`: the plan with the least workspace (512-row tiles and the 128 x 128 adapter kernel at M > 32).
+int make_plan(bool bwd, int64_t M, int64_t N, int64_t K, int64_t r, bool fewest, SlimPlan* p) {
   if (M < 1 || N < 16 || K < 128 || M >= kMaxDim || N >= kMaxDim || K >= kMaxDim) return SLIM_ESHAPE;
   if (N % 16 || K % 128 || r < 0 || r % 16 || r >= kMaxDim) return SLIM_ESHAPE;
   if (bwd && N % 128) return SLIM_ESHAPE;
@@ -107,42 +169,67 @@ int slim_make_plan(bool bwd, int64_t M, int64_t N, int64_t K, int64_t r, SlimPla
     if (red > kMaxLargeRed || cdiv(M, 32) * 32 * r >= kMaxTiledElems || cdiv(rows, 32) * 32 * r >= kMaxTiledElems)
       return SLIM_EUNSUPPORTED;
     q.decode = false;
-    q.sp_rows_tile = 512;
-    q.sp_row_tiles = cdiv(rows, 512);
-    // 512 x 128 tiles spend less dequantisation per MFMA (a tile takes about 1.12x the time of a
-    // 512 x 96 one for 4/3 the work); 512 x 96 tiles are more and can fill the last round of
-    // blocks (one per CU) better. Take the one with fewer rounds, weighted.
-    const int64_t r96 = cdiv(q.sp_row_tiles * cdiv(M, 96), 256), r128 = cdiv(q.sp_row_tiles * cdiv(M, 128), 256);
-    q.sp_cols_tile = 112 * r128 <= 100 * r96 ? 128 : 96;
-    q.sp_col_tiles = cdiv(M, q.sp_cols_tile);
-    q.sp_split = 1;
-    q.sp_chunks_per_split = nchunks;
-    // 256 x 256 adapter tiles (half the operand bytes per flop) with a 128 KiB ring, one block per
-    // CU, when they fill the 256 CUs with reduction slices of at least 2048: the long reductions
-    // at large M (the 70B dX product took 320 -> 253 us with its split sum; the 13B layers, whose
-    // slices would be shorter or whose blocks too few, were slower); 256 rows of the reduction
-    // stay within 32-bit byte offsets
-    const int64_t wtiles = cdiv(M, 256) * (r / 256);
-    const int64_t wsplit = wtiles > 0 ? std::max<int64_t>(1, std::min<int64_t>(256 / wtiles, red / 1024)) : 0;
-    if (r > 0 && r % 256 == 0 && red < (int64_t(1) << 22) && wtiles * wsplit >= 256 && red / wsplit >= 2048) {
-      q.ad_wide = true;
-      q.ad_tiles_m = (int)cdiv(M, 256);
-      q.ad_tiles_j = (int)(r / 256);
-      const int64_t slice = cdiv(cdiv(red, wsplit), 32) * 32;
-      q.ad_split = (int)cdiv(red, slice);
-      q.ad_slice = slice;
-      if (q.ad_split > 1) tpart_bytes = (size_t)q.ad_split * (size_t)cdiv(M, 32) * 32 * (size_t)r * 4;
-    } else if (r > 0) {
-      q.ad_tiles_m = (int)cdiv(M, 128);
-      q.ad_tiles_j = (int)cdiv(r, 128);
-      const int64_t tiles = (int64_t)q.ad_tiles_m * q.ad_tiles_j;
-      // two blocks per CU (the GEMM's LDS ring takes 64 KB): at most 512 blocks, so one round
-      const int64_t split = std::max<int64_t>(1, std::min<int64_t>(512 / tiles, red / 512));
-      const int64_t slice = cdiv(cdiv(red, split), 64) * 64;
-      q.ad_split = (int)cdiv(red, slice);
-      q.ad_slice = slice;
-      // split partials: fp32, one T-sized tiled array per split (summed by the next kernel)
-      if (q.ad_split > 1) tpart_bytes = (size_t)q.ad_split * (size_t)cdiv(M, 32) * 32 * (size_t)r * 4;
+    if (!fewest && mid_plan(bwd, M, rows, red, r, &q)) {
+      if (q.sp_split > 1 || r > 0)
+        ypart_bytes = (size_t)q.sp_split * (size_t)(q.sp_row_tiles * q.sp_rows_tile) * (size_t)(q.sp_col_tiles * q.sp_cols_tile) * 4;
+      if (q.ad_split > 1) {
+        ad_counters = (size_t)q.ad_tiles_m * q.ad_tiles_j;
+        tpart_bytes = ad_counters * q.ad_split * 128 * q.sp_cols_tile * 4;
+      }
+    }
+    if (!q.mid) {
+      q.sp_rows_tile = 512;
+      q.sp_row_tiles = cdiv(rows, 512);
+      // 512 x 128 tiles spend less dequantisation per MFMA (a tile takes about 1.12x the time of a
+      // 512 x 96 one for 4/3 the work); 512 x 96 tiles are more and can fill the last round of
+      // blocks (one per CU) better. Take the one with fewer rounds, weighted.
+      const int64_t r96 = cdiv(q.sp_row_tiles * cdiv(M, 96), 256), r128 = cdiv(q.sp_row_tiles * cdiv(M, 128), 256);
+      q.sp_cols_tile = 112 * r128 <= 100 * r96 ? 128 : 96;
+      q.sp_col_tiles = cdiv(M, q.sp_cols_tile);
+      q.sp_split = 1;
+      q.sp_chunks_per_split = nchunks;
+      // 256 x 256 adapter tiles (half the operand bytes per flop) with a 128 KiB ring, one block per
+      // CU, when they fill the 256 CUs with reduction slices of at least 2048: the long reductions
+      // at large M (the 70B dX product took 320 -> 253 us with its split sum; the 13B layers, whose
+      // slices would be shorter or whose blocks too few, were slower); 256 rows of the reduction
+      // stay within 32-bit byte offsets
+      const int64_t wtiles = cdiv(M, 256) * (r / 256);
+      const int64_t wsplit = wtiles > 0 ? std::max<int64_t>(1, std::min<int64_t>(256 / wtiles, red / 1024)) : 0;
+      if (r > 0 && r % 256 == 0 && red < (int64_t(1) << 22) && wtiles * wsplit >= 256 && red / wsplit >= 2048) {
+        q.ad_wide = true;
+        q.ad_tiles_m = (int)cdiv(M, 256);
+        q.ad_tiles_j = (int)(r / 256);
+        const int64_t slice = cdiv(cdiv(red, wsplit), 32) * 32;
+        q.ad_split = (int)cdiv(red, slice);
+        q.ad_slice = slice;
+        if (q.ad_split > 1) tpart_bytes = (size_t)q.ad_split * (size_t)cdiv(M, 32) * 32 * (size_t)r * 4;
+      } else if (r > 0 && !fewest && cdiv(M, 128) * cdiv(r, 128) <= 64) {
+        // few tiles of T: the middle path's first-product units, which sum their slices in the launch (7B
+        // prefill 11008 x 4096, M 2048, r 384 (48 tiles): 20.0 against 19.4 us and a 5.3 us launch that sums;
+        // 28672 x 8192, M 512 (16): 20.8 against 17.6 + 6.0). With more tiles two 128 x 128 blocks per CU are
+        // as fast or faster (4096 x 11008, M 3000, r 400 (96): 68 against 50 + 6; 13B layers at M 4096 equal).
+        q.ad_tn = true;
+        q.ad_tiles_m = (int)cdiv(M, 128);
+        q.ad_tiles_j = (int)cdiv(r, 128);
+        const int64_t tiles = (int64_t)q.ad_tiles_m * q.ad_tiles_j;
+        q.ad_slice = cdiv(cdiv(red, adapter_slices(tiles, red)), 64) * 64;
+        q.ad_split = (int)cdiv(red, q.ad_slice);
+        if (q.ad_split > 1) {
+          ad_counters = (size_t)tiles;
+          tpart_bytes = (size_t)tiles * q.ad_split * 128 * 128 * 4;
+        }
+      } else if (r > 0) {
+        q.ad_tiles_m = (int)cdiv(M, 128);
+        q.ad_tiles_j = (int)cdiv(r, 128);
+        const int64_t tiles = (int64_t)q.ad_tiles_m * q.ad_tiles_j;
+        // two blocks per CU (the GEMM's LDS ring takes 64 KB): at most 512 blocks, so one round
+        const int64_t split = std::max<int64_t>(1, std::min<int64_t>(512 / tiles, red / 512));
+        const int64_t slice = cdiv(cdiv(red, split), 64) * 64;
+        q.ad_split = (int)cdiv(red, slice);
+        q.ad_slice = slice;
+        // split partials: fp32, one T-sized tiled array per split (summed by the next kernel)
+        if (q.ad_split > 1) tpart_bytes = (size_t)q.ad_split * (size_t)cdiv(M, 32) * 32 * (size_t)r * 4;
+      }
     }
   }
   // workspace: [counters][adapter intermediate fp16 M x r][adapter partials][sparse partials]
@@ -173,8 +260,16 @@ int slim_make_plan(bool bwd, int64_t M, int64_t N, int64_t K, int64_t r, SlimPla
   q.off_pb = off;
   if (!q.decode && bwd) off = round256(off + (size_t)cdiv(rows, 32) * 32 * (size_t)r * 2);
   q.total = off;
+  // sizes that fit the no-allocation entry point's scratch on the 512-row tiles keep fitting
+  if ((q.mid || q.ad_tn) && q.total > (size_t)SLIM_NOALLOC_SCRATCH_BYTES) return make_plan(bwd, M, N, K, r, true, p);
   *p = q;
   return SLIM_OK;
+}
+
+}  // namespace
+
+int slim_make_plan(bool bwd, int64_t M, int64_t N, int64_t K, int64_t r, SlimPlan* p) {
+  return make_plan(bwd, M, N, K, r, false, p);
 }
 
 int slim_check_linear(bool bwd, const void* X, int xdtype, int64_t M, int64_t N, int64_t K, const void* codes,

@@ -1328,13 +1328,47 @@ int launch_layer(const LayerArgs& a, const SlimPlan& p, const uint16_t* act, int
 #undef SLIM_ROWPREP
     if (hipGetLastError() != hipSuccess) return SLIM_EDEVICE;
   }
+  if (p.mid || p.ad_tn) {
+    SlimMidArgs g;
+    g.codes = a.codes;
+    g.meta = a.meta;
+    g.scales = a.scales;
+    g.act16 = a.act16;
+    g.rowinv = a.rowinv;
+    g.out = a.out;
+    g.part = p.sp_split > 1 || a.r > 0 ? a.part : nullptr;
+    g.M = a.M;
+    g.rows = a.rows;
+    g.red = a.red;
+    g.r = a.r;
+    g.tile_cols = p.sp_cols_tile;
+    g.row_tiles = p.sp_row_tiles;
+    g.col_tiles = p.sp_col_tiles;
+    g.row_frags = p.sp_row_tiles * (p.sp_rows_tile / 32);
+    g.col_frags = p.sp_col_tiles * (p.sp_cols_tile / 32);
+    g.split = p.sp_split;
+    g.chunks = p.sp_chunks_per_split;
+    g.ad_q = a.ad_q;
+    g.ad_p = a.q4 ? a.ad_pb : a.ad_p;
+    g.p_tiled = a.p_tiled;
+    g.tm = a.tm;
+    g.tpart = a.tpart;
+    g.tcounters = a.tcounters;
+    g.ad_split = p.ad_split;
+    g.ad_slice = p.ad_slice;
+    g.ad_units = a.r > 0 ? (int64_t)p.ad_tiles_m * p.ad_tiles_j * p.ad_split : 0;
+    g.ad_blocks = (g.ad_units + 7) / 8 * 8;
+    if (p.mid) return slim_launch_mid(g, BWD, s);
+    int st = slim_launch_adapter_tn(g, s);
+    if (st != SLIM_OK) return st;
+  }
   if (a.r > 0) {
-    int st = slim_launch_adapter_gemm(a.act16, a.M, a.red, a.ad_q, a.r, p, ws, s);
+    int st = p.ad_tn ? SLIM_OK : slim_launch_adapter_gemm(a.act16, a.M, a.red, a.ad_q, a.r, p, ws, s);
     if (st != SLIM_OK) return st;
     // the factor needs re-laying only when given row-major (backward); tm needs summing only
     // when the GEMM split its reduction
     const int64_t np = a.p_tiled ? 0 : (a.rows * a.r / 8 + 255) / 256;
-    const int64_t nt = p.ad_split > 1 ? ((a.M + 31) / 32 * 32 * a.r / 8 + 255) / 256 : 0;
+    const int64_t nt = p.ad_split > 1 && !p.ad_tn ? ((a.M + 31) / 32 * 32 * a.r / 8 + 255) / 256 : 0;
     if (np + nt > 0) {
       SlimKernelTimer timer("adapter_finish", s);
       SLIM_LAUNCH(timer, k_adapter_finish, dim3((unsigned)(np + nt)), dim3(256), s,

@@ -146,3 +146,40 @@ def test_noalloc_refuses_sizes_past_its_scratch_before_touching_a_device():
     # argument errors are reported the same way as by slim_linear
     assert slim.slim_linear_noalloc(A, 1, 16, 100, 512, A, A, A, None, None, 0, A, None) == slim.SLIM_ESHAPE
     assert "noalloc" in " ".join(slim.header_symbols())
+
+
+def _rows512_workspace(M, N, K, r):
+    """Bytes of a forward call on the 512-row tiles with the 128 x 128 adapter kernel: counters, T, its
+    fp32 slice partials, the fp16 activations and the row scales."""
+    c = lambda a, b: -(-a // b)
+    up = lambda x: (x + 255) // 256 * 256
+    m32 = c(M, 32) * 32
+    off = up(4096 * 4 + m32 * r * 2)
+    if r:
+        wt = c(M, 256) * (r // 256)
+        ws = max(1, min(256 // wt, K // 1024)) if wt else 0
+        if r % 256 == 0 and wt * ws >= 256 and K // ws >= 2048:
+            split = c(K, c(c(K, ws), 32) * 32)
+        else:
+            s = max(1, min(512 // (c(M, 128) * c(r, 128)), K // 512))
+            split = c(K, c(c(K, s), 64) * 64)
+        off = up(off + (split * m32 * r * 4 if split > 1 else 0))
+    return up(up(off + M * K * 2) + M * 4)
+
+
+def test_sizes_that_fit_the_noalloc_scratch_on_512_row_tiles_still_fit():
+    # the middle path's partials and slices may take more workspace, but never push a size out of the scratch
+    import random
+    rng = random.Random(5)
+    lim = slim.SLIM_NOALLOC_SCRATCH_BYTES
+    near = 0
+    for _ in range(20000):
+        n, k = 16 * rng.randint(1, 1800), 128 * rng.randint(1, 224)
+        m = rng.randint(33, 8192) if rng.random() < 0.5 else rng.randint(33, 700)
+        r = 16 * rng.randint(0, 64)
+        base, now = _rows512_workspace(m, n, k, r), slim.slim_linear_workspace(m, n, k, r)
+        near += now != base
+        assert now == base or now <= lim, (m, n, k, r, base, now)
+        if base <= lim:
+            assert now <= lim, (m, n, k, r, base, now)
+    assert near > 1000
