@@ -253,9 +253,19 @@ def slim_timing_read() -> dict:
 
 # ------------------------------------------------------------------ tensor helpers
 
+# The helpers below run on every layer call, whose kernels take about 10 us on the smallest layers, so they
+# are kept short: a 4096 x 4096 call at one row took 16.1 us through ``linear`` with a torch stream object and
+# a device object made twice per call (2.6 and 0.6 us each), against 9.2 us for its C call alone; it takes 11.1
+# us with the raw stream handle.
+_torch_mod = None
+
+
 def _torch():
-    import torch
-    return torch
+    global _torch_mod
+    if _torch_mod is None:
+        import torch
+        _torch_mod = torch
+    return _torch_mod
 
 
 def _ptr(t):
@@ -263,18 +273,24 @@ def _ptr(t):
 
 
 def _stream(stream=None):
+    """The hipStream_t of `stream`, or of the current device's current stream."""
+    if stream is not None:
+        return stream.cuda_stream
     torch = _torch()
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return s.cuda_stream
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    if raw is None:
+        return torch.cuda.current_stream().cuda_stream
+    return raw(torch.cuda.current_device())
 
 
 def _dtype_code(t) -> int:
     torch = _torch()
-    if t.dtype == torch.bfloat16:
+    dt = t.dtype
+    if dt is torch.bfloat16:
         return SLIM_BF16
-    if t.dtype == torch.float16:
+    if dt is torch.float16:
         return SLIM_F16
-    raise TypeError(f"activations must be bf16 or fp16, got {t.dtype}")
+    raise TypeError(f"activations must be bf16 or fp16, got {dt}")
 
 
 def _on_gpu(*ts):
@@ -289,7 +305,7 @@ _ws_cache: dict = {}
 def workspace(nbytes: int, device=None, stream=None):
     """A zero-initialised workspace of at least nbytes, cached per (device, stream)."""
     torch = _torch()
-    dev = torch.device(device if device is not None else "cuda")
+    dev = device if isinstance(device, torch.device) else torch.device(device if device is not None else "cuda")
     key = (dev, _stream(stream))
     ws = _ws_cache.get(key)
     if ws is None or ws.numel() < nbytes:
