@@ -388,6 +388,182 @@ k_grad_w(const uint16_t* __restrict__ dY, const uint16_t* __restrict__ X, int64_
   }
 }
 
+// 128 (k) x 128 (n) tiles for small layers, where 256 x 256 tiles are too few for the chip. Eight waves in two
+// groups: each 32-row chunk is two 16-row steps of the reduction and group g takes step g, as 2 x 2 waves of
+// 64 x 64 (2 x 2 fragments), so a tile's chain along M is half as long and a SIMD has two waves to hide
+// waits with; group 1's sums go through LDS to group 0 at the end (a fixed order). Per chunk 8 KiB of X and of
+// dY go to LDS by direct loads into four slots (rows of 256 bytes, 32-byte pieces XOR-swizzled as above); a
+// chunk's fragments are read transposed while the MFMAs of the chunk before run, so a slot is free, and
+// refilled four chunks ahead, once every wave has passed the next barrier. Bound by the chain of M / 32 chunks
+// where tiles are few (about 0.2 us a chunk): 1000 x 3072 x 768 takes 16.3 us (256 x 256 tiles: 29.4), 2048 x
+// 768 x 3072 23 (45), 8192 x 4096 x 1024 77 (144, now 890 TFLOP/s).
+constexpr int kSGT = 128;
+
+SLIM_DEV uint32_t gs_off(int r, int c) {
+  return (uint32_t)r * 256u + ((uint32_t)(((c >> 4) ^ (2 * (r & 3))) << 5)) + (uint32_t)((c & 15) * 2);
+}
+
+template <bool BF16>
+__global__ void __launch_bounds__(kGThreads, 2)
+k_grad_w_small(const uint16_t* __restrict__ dY, const uint16_t* __restrict__ X, int64_t M, int64_t N, int64_t K,
+               const uint8_t* __restrict__ meta, float* __restrict__ gW) {
+  // slots of 8 KiB: X chunks [m][k] at 0, dY chunks [m][n] at 32 KiB; group 1's sums take all 64 KiB at the end
+  constexpr uint32_t kSlot = kGM * kSGT * 2, kYBase = kGRing * kSlot;
+  __shared__ __attribute__((aligned(16))) uint8_t lds[2 * kGRing * kSlot];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int grp = wave >> 2, wk = wave & 1, wn = (wave >> 1) & 1, h = lane >> 5;
+  // k tiles fastest within an XCD's run (block b runs on XCD b % 8), so its blocks share dY slabs in its L2
+  const uint32_t tk = (uint32_t)((K + kSGT - 1) / kSGT), T = (uint32_t)((N + kSGT - 1) / kSGT) * tk, Q = (T + 7) / 8;
+  const uint32_t pos = (blockIdx.x % 8) * Q + blockIdx.x / 8;
+  if (pos >= T) return;
+  const int64_t n0 = (int64_t)(pos / tk) * kSGT, k0 = (int64_t)(pos % tk) * kSGT;
+
+  // direct loads: one 1 KiB piece (rows 4 wave .. + 3) of X and one of dY per wave and chunk; lane L writes LDS
+  // bytes 16 L of the piece, row 4 wave + L / 16 at physical 16-byte slot L % 16, which holds logical slot
+  // (L % 16) ^ (4 (row % 4)). Rows past M lie past the resources and read as zero.
+  const rsrc_t ry = make_rsrc(dY, M * N * 2), rx = make_rsrc(X, M * K * 2);
+  const int row = 4 * wave + (lane >> 4), ls = (lane & 15) ^ (4 * (row & 3));
+  const uint32_t xo = ((uint32_t)row * (uint32_t)K + (uint32_t)(k0 + 8 * ls)) * 2u;
+  const uint32_t yo = ((uint32_t)row * (uint32_t)N + (uint32_t)(n0 + 8 * ls)) * 2u;
+  const uint32_t xstep = (uint32_t)kGM * (uint32_t)K * 2u, ystep = (uint32_t)kGM * (uint32_t)N * 2u;
+  const int nch = (int)((M + kGM - 1) / kGM);
+  auto issue = [&](int c, auto zc) {
+    // past the end: a dead slot, loaded from past the resource (no memory access)
+    constexpr uint32_t z = decltype(zc)::value;
+    const bool in = c < nch;
+    const uint32_t cc = (uint32_t)(in ? c : 0);
+    uint8_t* D = lds + z * kSlot + (uint32_t)wave * 1024u;
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (lds_ptr_t)D, 16, in ? xo + cc * xstep : 0xFFFFFFF0u, 0, 0, 0);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(ry, (lds_ptr_t)(D + kYBase), 16, in ? yo + cc * ystep : 0xFFFFFFF0u, 0, 0, 0);
+  };
+
+  f16_t acc[2][2];
+#pragma unroll
+  for (int x = 0; x < 2; ++x)
+#pragma unroll
+    for (int y = 0; y < 2; ++y)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[x][y][v] = 0.f;
+  auto rd_tr = [](uint32_t addr, auto oc) -> u32x2_t {
+    u32x2_t v;
+    asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(v) : "v"(addr), "i"(decltype(oc)::value));
+    return v;
+  };
+  // the lane's read addresses in slot 0: rows of the group's step (see k_grad_w for the lane mapping)
+  const int G = lane >> 4, q = lane & 15;
+  const int rr = 16 * grp + 8 * (G >> 1) + (q >> 2), cr = 16 * (G & 1) + 4 * (q & 3);
+  const uint32_t lb = (uint32_t)(uintptr_t)(lds_ptr_t)&lds[0];
+  uint32_t ax[2][2], by[2][2];           // [fragment][read]
+#pragma unroll
+  for (int j = 0; j < 2; ++j)
+#pragma unroll
+    for (int f = 0; f < 2; ++f) {
+      ax[f][j] = lb + gs_off(rr + 4 * j, 64 * wk + 32 * f + cr);
+      by[f][j] = lb + kYBase + gs_off(rr + 4 * j, 64 * wn + 32 * f + cr);
+    }
+  struct Frags {
+    u32x2_t a[2][2], b[2][2];
+  };
+  auto read = [&](Frags& F, auto zc) {
+    using off = std::integral_constant<uint32_t, decltype(zc)::value * kSlot>;
+#pragma unroll
+    for (int f = 0; f < 2; ++f)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        F.a[f][j] = rd_tr(ax[f][j], off{});
+        F.b[f][j] = rd_tr(by[f][j], off{});
+      }
+  };
+  auto landed = [](Frags& F) {
+    asm volatile("s_waitcnt lgkmcnt(0)"
+                 : "+v"(F.a[0][0]), "+v"(F.a[0][1]), "+v"(F.a[1][0]), "+v"(F.a[1][1]), "+v"(F.b[0][0]), "+v"(F.b[0][1]),
+                   "+v"(F.b[1][0]), "+v"(F.b[1][1]));
+  };
+  Frags F[2];
+  // Chunk c in slot z, its fragments in set f: chunk c + 1 has landed once only chunks c + 2 and c + 3 are
+  // outstanding (4 loads); after the barrier no wave reads chunk c's slot.
+  auto chunk = [&](int c, auto zc, auto fc) {
+    constexpr int z = decltype(zc)::value, f = decltype(fc)::value;
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_waitcnt(vmcnt_lgkm0_wait(4));
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+    read(F[f ^ 1], std::integral_constant<int, (z + 1) % kGRing>{});
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int x = 0; x < 2; ++x)
+#pragma unroll
+      for (int y = 0; y < 2; ++y) {
+        const u32x4_t av = {F[f].a[x][0][0], F[f].a[x][0][1], F[f].a[x][1][0], F[f].a[x][1][1]};
+        const u32x4_t bv = {F[f].b[y][0][0], F[f].b[y][0][1], F[f].b[y][1][0], F[f].b[y][1][1]};
+        acc[x][y] = mfma_acc<BF16>(av, bv, acc[x][y]);
+        __builtin_amdgcn_sched_barrier(0);
+        if (x == 0 && y == 0) issue(c + 4, zc);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    landed(F[f ^ 1]);
+  };
+  using I0 = std::integral_constant<int, 0>;
+  using I1 = std::integral_constant<int, 1>;
+  using I2 = std::integral_constant<int, 2>;
+  using I3 = std::integral_constant<int, 3>;
+  issue(0, I0{});
+  issue(1, I1{});
+  issue(2, I2{});
+  issue(3, I3{});
+  __builtin_amdgcn_s_waitcnt(vmcnt_lgkm0_wait(6));
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_sched_barrier(0);
+  read(F[0], I0{});
+  landed(F[0]);
+  // chunks past the last read zeros, so whole groups of four need no guards
+  for (int c = 0; c < nch; c += 4) {
+    chunk(c, I0{}, I0{});
+    chunk(c + 1, I1{}, I1{});
+    chunk(c + 2, I2{}, I0{});
+    chunk(c + 3, I3{}, I1{});
+  }
+  // no direct load may still be writing LDS when its slots are reused
+  __builtin_amdgcn_s_waitcnt(0);
+  __syncthreads();
+  f4_t* hand = reinterpret_cast<f4_t*>(lds) + (uint32_t)(wave & 3) * 1024u;
+  if (grp == 1) {
+#pragma unroll
+    for (int x = 0; x < 2; ++x)
+#pragma unroll
+      for (int y = 0; y < 2; ++y)
+#pragma unroll
+        for (int q4 = 0; q4 < 4; ++q4) {
+          const f4_t v = {acc[x][y][4 * q4], acc[x][y][4 * q4 + 1], acc[x][y][4 * q4 + 2], acc[x][y][4 * q4 + 3]};
+          hand[((2 * x + y) * 4 + q4) * 64 + lane] = v;
+        }
+  }
+  __syncthreads();
+  if (grp == 1) return;
+#pragma unroll
+  for (int y = 0; y < 2; ++y) {
+    const int64_t n = n0 + 64 * wn + 32 * y + (lane & 31);
+#pragma unroll
+    for (int x = 0; x < 2; ++x) {
+      const int64_t gb = (k0 + 64 * wk + 32 * x) / 4;
+      const uint32_t md = *reinterpret_cast<const uint32_t*>(meta + n * (K / 8) + gb / 2);
+#pragma unroll
+      for (int q4 = 0; q4 < 4; ++q4) {
+        const f4_t o = hand[((2 * x + y) * 4 + q4) * 64 + lane];
+        f16_t s = acc[x][y];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) s[4 * q4 + e] += o[e];
+        const int t = 2 * q4 + h;                               // group gb + t holds rows 8 q4 + 4h ..
+        const uint32_t nib = (md >> (4 * t)) & 0xFu;
+        const float v0 = sel4(s, 4 * q4, (int)(nib & 3u)), v1 = sel4(s, 4 * q4, (int)(nib >> 2));
+        *reinterpret_cast<u32x2_t*>(gW + n * (K / 2) + 2 * (gb + t)) =
+            u32x2_t{__builtin_bit_cast(uint32_t, v0), __builtin_bit_cast(uint32_t, v1)};
+      }
+    }
+  }
+}
+
 // ------------------------------------------------------------------ sparse add and update
 // out = beta A + gamma B elementwise (fp32: beta A rounded, then fused with gamma B); four
 // elements per thread.
@@ -474,6 +650,22 @@ extern "C" int slim_grad_w(const void* dY, const void* X, int dtype, int64_t M, 
   const int64_t T = ((N + kGT - 1) / kGT) * ((K + kGT - 1) / kGT);
   const dim3 grid((unsigned)(8 * ((T + 7) / 8)));
   SlimKernelTimer timer("grad_w", s);
+  // Up to 128 tiles of 256 x 256 leave half of the 256 CUs idle, and four times as many of 128 x 128, two
+  // blocks to a CU, are faster or level: 36 of the large (1000 x 3072 x 768) 29 -> 16 us, 128 of them (8192 x
+  // 4096 x 2048) 147 -> 144, (2048 x 2048 x 4096) 47 -> 45; at 144 (8192 x 3072 x 3072) 152 -> 205 (kernel
+  // times, launch included). Rows past M are told from the ends of the operands there, so their 32-bit
+  // offsets may not wrap either.
+  if (T <= 128 && (M + kGM) * (N > K ? N : K) * 2 < (int64_t(1) << 32)) {
+    const int64_t Ts = ((N + kSGT - 1) / kSGT) * ((K + kSGT - 1) / kSGT);
+    const dim3 sgrid((unsigned)(8 * ((Ts + 7) / 8)));
+    if (dtype == SLIM_BF16)
+      SLIM_LAUNCH(timer, k_grad_w_small<true>, sgrid, dim3(kGThreads), s, reinterpret_cast<const uint16_t*>(dY),
+                  reinterpret_cast<const uint16_t*>(X), M, N, K, meta, gW);
+    else
+      SLIM_LAUNCH(timer, k_grad_w_small<false>, sgrid, dim3(kGThreads), s, reinterpret_cast<const uint16_t*>(dY),
+                  reinterpret_cast<const uint16_t*>(X), M, N, K, meta, gW);
+    return hipGetLastError() == hipSuccess ? SLIM_OK : SLIM_EDEVICE;
+  }
   if (dtype == SLIM_BF16)
     SLIM_LAUNCH(timer, k_grad_w<true>, grid, dim3(kGThreads), s, reinterpret_cast<const uint16_t*>(dY),
                 reinterpret_cast<const uint16_t*>(X), M, N, K, meta, gW);

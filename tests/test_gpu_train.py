@@ -86,6 +86,15 @@ def test_grad_w_parity(m, n, k, dtype):
     assert np.all(np.abs(g - ref) <= _grad_bound(dYv, Xv, meta, n, k))
 
 
+# The last group of four 32-row chunks of the 128 x 128 tiles, their largest grid (128 tiles of 256 x 256), and
+# the first grids past it, with ragged rows and half tiles along N and K.
+@pytest.mark.parametrize("m,n,k", [(31, 128, 256), (32, 256, 128), (96, 384, 128), (129, 128, 128), (255, 256, 256),
+                                   (33, 2048, 4096), (33, 2176, 3840), (70, 3840, 2432)])
+@pytest.mark.parametrize("dtype", ["bf16", "fp16"])
+def test_grad_w_tile_sizes(m, n, k, dtype):
+    test_grad_w_parity(m, n, k, dtype)
+
+
 def test_grad_w_full_size_sampled_rows():
     # 70B MLP projection: dY [8192 x 28672], X [8192 x 8192], compressed gradient [28672 x 4096]
     m, n, k = 8192, 28672, 8192
