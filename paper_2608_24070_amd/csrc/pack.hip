@@ -8,211 +8,213 @@ namespace {
 
 constexpr int kPackThreads = 256;
 
-// One thread per aligned 4-group of one row; the 32 threads of a half-wave cover one
-// 128-wide quantisation group (rows hold K/4 groups and K % 128 == 0, so groups never
-// straddle half-waves). With `alpha` (one float64 in device memory, SLiM-Quant's per-tensor
-// parameter) every group takes it in place of its own absmax.
+// |x / s| rounded to the nearest integer, ties to even, at most 7: exactly the clamped rint of the quotient,
+// without a division. r is 1 / s to an ulp, so the first guess is off by at most one, and only next to a
+// half-way point. t - q s is then exact in fp32 (q s has 15 bits; for q >= 1 the difference, below s, is a
+// multiple of t's last place, at least 2^-25 s), so it can be compared with s / 2 = hs; on an odd q a tie moves
+// on to the even neighbour, which the bit pattern one below hs makes part of the same comparison.
+SLIM_DEV uint32_t round_mag(float t, float s, float r, uint32_t hs) {
+  const float q = rintf(fminf(t * r, 7.0f));
+  const float d = fmaf(-q, s, t);
+  const int qi = (int)q;
+  const int step = fabsf(d) > __uint_as_float(hs - (uint32_t)(qi & 1)) ? ((int)__float_as_uint(d) >> 31) | 1 : 0;
+  return (uint32_t)min(qi + step, 7);
+}
+
+// One thread per 16 positions of a row (four 4-groups, one code word and one index half-word); eight threads
+// cover one 128-wide quantisation group, whose absmax takes three exchanges and whose division by 7 and
+// reciprocal are made once for eight codes. With `alpha` (one float64 in device memory, SLiM-Quant's
+// per-tensor parameter) every group takes it in place of its own absmax. Bound by the reading of W (11008 x
+// 4096: 74 us with a thread per 4-group and two float64 divisions in each, 38 now).
 __global__ void __launch_bounds__(kPackThreads)
-k_pack(const float4* __restrict__ W, int64_t total4, int64_t K, uint32_t* __restrict__ codes,
-       uint16_t* __restrict__ meta, uint16_t* __restrict__ scales, uint32_t* __restrict__ mask,
+k_pack(const u32x4_t* __restrict__ W, int64_t total16, int64_t nch, uint32_t* __restrict__ codes,
+       uint16_t* __restrict__ meta, uint16_t* __restrict__ scales, u32x4_t* __restrict__ mask,
        int* __restrict__ status, const double* __restrict__ alpha) {
   const int64_t t = (int64_t)blockIdx.x * kPackThreads + threadIdx.x;
-  const bool valid = t < total4;
-  float4 v = valid ? W[t] : make_float4(0.f, 0.f, 0.f, 0.f);
-  const float w[4] = {v.x, v.y, v.z, v.w};
-  float a[4];
-  int bad = 0;
+  if (t >= total16) return;                  // total16 is a multiple of 8: whole groups stay together
+  u32x4_t v[4];
 #pragma unroll
-  for (int p = 0; p < 4; ++p) {
-    a[p] = fabsf(w[p]);
-    if (!__builtin_isfinite(w[p])) bad = 1;
-  }
-  // group absmax over the 32 lanes of this half-wave
-  float gmax = fmaxf(fmaxf(a[0], a[1]), fmaxf(a[2], a[3]));
+  for (int c = 0; c < 4; ++c) v[c] = W[4 * t + c];
+  // magnitudes order as their bit patterns, and a non-finite one is at least infinity's
+  uint32_t am = 0;
 #pragma unroll
-  for (int off = 16; off >= 1; off >>= 1) gmax = fmaxf(gmax, __shfl_xor(gmax, off, 32));
-  // s16 = fp16_RNE(fp32 absmax / 7), IEEE division (alpha rounded to fp32 in its place)
+  for (int c = 0; c < 4; ++c)
+#pragma unroll
+    for (int p = 0; p < 4; ++p) am = max(am, v[c][p] & 0x7FFFFFFFu);
+  int bad = am >= 0x7F800000u ? 1 : 0;
+#pragma unroll
+  for (int off = 4; off >= 1; off >>= 1) am = max(am, (uint32_t)__shfl_xor((int)am, off, 64));
+  float gmax = __uint_as_float(am);
   if (alpha) {
     const double ad = *alpha;
     if (!(ad >= 0.0)) bad |= 2;
     gmax = (float)ad;
   }
-  const float s32 = __fdiv_rn(gmax, 7.0f);
-  const _Float16 s16 = (_Float16)s32;
-  const uint16_t s16bits = __builtin_bit_cast(uint16_t, s16);
-  if (!__builtin_isfinite((float)s16)) bad |= 2;
-  if (valid && bad) atomicOr(status, bad);
+  // s16 = fp16_RNE(fp32 absmax / 7), IEEE division (alpha rounded to fp32 in its place)
+  const _Float16 s16 = (_Float16)__fdiv_rn(gmax, 7.0f);
+  const float sf = (float)s16;
+  if (!__builtin_isfinite(sf)) bad |= 2;
+  if (bad) atomicOr(status, bad);
+  const bool pos = sf > 0.f;
+  const float r = __builtin_amdgcn_rcpf(sf);
+  const uint32_t hs = __float_as_uint(0.5f * sf);
 
-  // top-2 of the four by (|w| desc, position asc)
-  int keep[4];
+  uint32_t cw = 0, mw = 0, mk[4];
 #pragma unroll
-  for (int p = 0; p < 4; ++p) {
-    int rank = 0;
+  for (int c = 0; c < 4; ++c) {
+    float w[4], a[4];
 #pragma unroll
-    for (int q = 0; q < 4; ++q)
-      if (q != p && (a[q] > a[p] || (a[q] == a[p] && q < p))) ++rank;
-    keep[p] = rank < 2;
-  }
-  int i0 = -1, i1 = -1;
-#pragma unroll
-  for (int p = 0; p < 4; ++p)
-    if (keep[p]) {
-      if (i0 < 0) i0 = p;
-      else i1 = p;
+    for (int p = 0; p < 4; ++p) {
+      w[p] = __uint_as_float(v[c][p]);
+      a[p] = fabsf(w[p]);
     }
-  const double sd = (double)s16;
-  auto code = [&](float x) -> uint32_t {
-    if (!(sd > 0.0)) return 8u;
-    double q = rint((double)x / sd);
-    q = fmin(7.0, fmax(-7.0, q));
-    return (uint32_t)((int)q + 8);
-  };
-  const uint32_t u0 = code(w[i0]);
-  const uint32_t u1 = code(w[i1]);
-  const int64_t j = t % (K / 4);          // group index inside the row
-  const int c = (int)(t & 3);             // group slot inside its 16-position block
-  uint32_t cw = (u0 << (4 * c)) | (u1 << (16 + 4 * c));
-  uint32_t mw = (uint32_t)(i0 | (i1 << 2)) << (4 * c);
-  cw |= __shfl_xor(cw, 1, 64);
-  mw |= __shfl_xor(mw, 1, 64);
-  cw |= __shfl_xor(cw, 2, 64);
-  mw |= __shfl_xor(mw, 2, 64);
-  if (!valid) return;
-  const int64_t row = t / (K / 4);
-  const int64_t slot = packed_slot(row, j >> 5, K / 128);   // word (j >> 2) & 7 of chunk j >> 5
-  if (c == 0) {
-    codes[8 * slot + ((j >> 2) & 7)] = cw;
-    meta[8 * slot + ((j >> 2) & 7)] = (uint16_t)mw;
+    // top two by (|w| desc, position asc): p < q comes first exactly when a[p] >= a[q]; kept are those that
+    // come before at least two of the other three
+    const bool c01 = a[0] >= a[1], c02 = a[0] >= a[2], c03 = a[0] >= a[3], c12 = a[1] >= a[2], c13 = a[1] >= a[3],
+               c23 = a[2] >= a[3];
+    auto two = [](bool x, bool y, bool z) { return (x & y) | (z & (x | y)); };
+    const bool k0 = two(c01, c02, c03), k1 = two(!c01, c12, c13), k2 = two(!c02, !c12, c23),
+               k3 = two(!c03, !c13, !c23);
+    const uint32_t i0 = k0 ? 0u : (k1 ? 1u : 2u), i1 = k3 ? 3u : (k2 ? 2u : 1u);
+    const float x0 = k0 ? w[0] : (k1 ? w[1] : w[2]), x1 = k3 ? w[3] : (k2 ? w[2] : w[1]);
+    auto code = [&](float x) -> uint32_t {
+      const int m = pos ? (int)round_mag(fabsf(x), sf, r, hs) : 0;
+      return (uint32_t)(8 + (__float_as_uint(x) >> 31 ? -m : m));
+    };
+    cw |= (code(x0) << (4 * c)) | (code(x1) << (16 + 4 * c));
+    mw |= (i0 | (i1 << 2)) << (4 * c);
+    mk[c] = (k0 ? 1u : 0u) | (k1 ? 1u << 8 : 0u) | (k2 ? 1u << 16 : 0u) | (k3 ? 1u << 24 : 0u);
   }
-  if ((j & 31) == 0) scales[slot] = s16bits;
-  if (mask) mask[t] = (uint32_t)keep[0] | ((uint32_t)keep[1] << 8) | ((uint32_t)keep[2] << 16) |
-                      ((uint32_t)keep[3] << 24);
+  // W holds fewer than 2^32 groups of 128 (2 TiB): a 32-bit division
+  const uint32_t g = (uint32_t)(t >> 3), row = g / (uint32_t)nch;
+  const int64_t slot = packed_slot(row, g - row * (uint32_t)nch, nch);
+  const int word = (int)(t & 7);
+  codes[8 * slot + word] = cw;
+  meta[8 * slot + word] = (uint16_t)mw;
+  if (word == 0) scales[slot] = __builtin_bit_cast(uint16_t, s16);
+  if (mask) mask[t] = u32x4_t{mk[0], mk[1], mk[2], mk[3]};
 }
 
-// Backward pack. Block = 256 threads, tile = 64 rows (n) x 64 columns (k).
-// Phase 1 decodes the forward pack of the tile into LDS; phase 2 gives each thread one
-// column k and one 16-row block, prunes each aligned 4-row group to its top two
-// (|Wc| desc, forward-kept desc, row asc) and emits one codesT word and one metaT half-word.
-constexpr int kBT = 64;
+// Backward pack. Block = 256 threads, tile = 128 rows (n) x 128 columns (k): whole slots of both packs, so
+// every load and store moves whole sectors. Phase 1 expands the tile into LDS, one byte per entry: its code
+// (8 where pruned) in bits 0..3, 3 - n % 4 in bits 4..5, the forward-kept bit in bit 6; a thread makes 16
+// columns of a row at a time, 16-byte LDS writes. Phase 2 gives each thread four columns (one LDS word per
+// row) and one 16-row block, prunes each aligned 4-row group to its top two (|Wc| desc, forward-kept desc,
+// row asc) and emits one codesT word and one metaT half-word per column. A key orders a group's entries in
+// one integer comparison: |code - 8| s16 is exact in fp32 with ten low bits zero (3-bit x 11-bit
+// significands), and the LDS byte fits below; the top two are a max / min network, and carry their codes.
+// LDS rows are 128 bytes with one row of padding per 16, and the words of a row XOR-swizzled by
+// 8 (n / 32 % 4), so the eight row blocks that a wave reads at once fall in distinct banks. Bound by
+// instruction issue and the latency of the three phases (11008 x 4096: 54 us with 64 x 64 tiles, byte
+// writes and fp32 ranking, 23 now; 34 MB).
+constexpr int kBT = 128;
 // Largest forward scale the backward accepts: its large-M path multiplies gradients scaled below
 // 2^(kActExp + 1) = 32 by s16 in fp16, which stays below 65504 for s16 < 2048.
 constexpr float kBwdScaleLimit = 2048.0f;
 static_assert(kActExp == 4, "kBwdScaleLimit assumes row-scaled activations below 32");
 
+// LDS word of columns 4 quad .. + 3 of row n
+SLIM_DEV int pb_word(int n, int quad) { return (n + (n >> 4)) * (kBT / 4) + (quad ^ (8 * ((n >> 5) & 3))); }
+
+template <bool MASK>
 __global__ void __launch_bounds__(256)
 k_pack_bwd(const uint32_t* __restrict__ codes, const uint16_t* __restrict__ meta,
            const uint16_t* __restrict__ scales, int64_t N, int64_t K, uint32_t* __restrict__ codesT,
            uint16_t* __restrict__ metaT, uint16_t* __restrict__ scalesT, uint8_t* __restrict__ mask_rc,
            int* __restrict__ status) {
-  __shared__ uint8_t u_s[kBT][kBT + 4];     // forward code per (row, col), 8 where pruned
-  __shared__ uint8_t f_s[kBT][kBT + 4];     // forward-kept bit, later the W^{R,C} support bit
-  __shared__ float sc_s[kBT];               // scale of each row for this column tile
+  __shared__ __attribute__((aligned(16))) uint32_t e_s[(kBT + kBT / 16) * (kBT / 4)];
+  __shared__ __attribute__((aligned(16))) float sc_s[kBT];     // |scale| of each row for this column tile
   const int tid = threadIdx.x;
-  const int64_t k0 = (int64_t)blockIdx.x * kBT;
-  const int64_t n0 = (int64_t)blockIdx.y * kBT;
-  const int rows = (int)min((int64_t)kBT, N - n0);   // multiple of 16 (N % 16 == 0)
+  const int64_t kc = blockIdx.x, nc = blockIdx.y, n0 = nc * kBT, k0 = kc * kBT;   // N and K are multiples of 128
 
-  // phase 1: thread -> (row = tid / 4, 16-column block w = tid % 4)
-  {
-    const int row = tid >> 2, w = tid & 3;
-    if (row < rows) {
-      const int64_t n = n0 + row;
-      // k0 is a multiple of 64: the tile's four 16-column blocks are words (k0 % 128) / 16 + w
-      // of chunk k0 / 128
-      const int64_t slot = packed_slot(n, k0 >> 7, K / 128);
-      const uint32_t cw = codes[8 * slot + ((k0 & 127) >> 4) + w];
-      const uint32_t mw = meta[8 * slot + ((k0 & 127) >> 4) + w];
+  // phase 1: thread -> (row tid / 8 + 32 j, word tid % 8)
+  uint32_t cws[4], mws[4];
 #pragma unroll
-      for (int p = 0; p < 16; ++p) {
-        u_s[row][16 * w + p] = 8;
-        f_s[row][16 * w + p] = 0;
-      }
+  for (int j = 0; j < 4; ++j) {
+    const int64_t slot = packed_slot(n0 + (tid >> 3) + 32 * j, kc, K / 128);
+    cws[j] = codes[8 * slot + (tid & 7)];
+    mws[j] = meta[8 * slot + (tid & 7)];
+  }
+  if (tid < kBT) {
+    const uint16_t sb = scales[packed_slot(n0 + tid, kc, K / 128)];
+    const float sc = h_bits_to_f(sb);
+    sc_s[tid] = fabsf(sc);
+    // the backward's fp16 product of a row-scaled gradient (below 32) and s16 must stay finite
+    if (!(sc < kBwdScaleLimit)) atomicOr(status, 2);
+    scalesT[kc * N + n0 + tid] = sb;
+  }
 #pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        const int i0 = (mw >> (4 * c)) & 3, i1 = (mw >> (4 * c + 2)) & 3;
-        u_s[row][16 * w + 4 * c + i0] = (cw >> (4 * c)) & 0xF;
-        u_s[row][16 * w + 4 * c + i1] = (cw >> (16 + 4 * c)) & 0xF;
-        f_s[row][16 * w + 4 * c + i0] = 1;
-        f_s[row][16 * w + 4 * c + i1] = 1;
-      }
-      if (w == 0) {
-        sc_s[row] = h_bits_to_f(scales[slot]);
-        // the backward's fp16 product of a row-scaled gradient (below 32) and s16 must stay finite
-        if (!(sc_s[row] < kBwdScaleLimit)) atomicOr(status, 2);
-      }
+  for (int j = 0; j < 4; ++j) {
+    const int row = (tid >> 3) + 32 * j;
+    u32x4_t e;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const uint32_t s0 = ((mws[j] >> (4 * c)) & 3u) * 8u, s1 = ((mws[j] >> (4 * c + 2)) & 3u) * 8u;
+      const uint32_t u0 = (cws[j] >> (4 * c)) & 0xFu, u1 = (cws[j] >> (16 + 4 * c)) & 0xFu;
+      uint32_t x = 0x08080808u;
+      x = (x & ~(0xFFu << s0)) | ((u0 | 0x40u) << s0);
+      x = (x & ~(0xFFu << s1)) | ((u1 | 0x40u) << s1);
+      e[c] = x | 0x10101010u * (uint32_t)(3 - (row & 3));
     }
+    *reinterpret_cast<u32x4_t*>(&e_s[pb_word(row, 4 * (tid & 7))]) = e;
   }
   __syncthreads();
 
-  // phase 2: thread -> (column col = tid / 4, 16-row block rb = tid % 4)
-  uint32_t sel16 = 0;
-  const int col = tid >> 2, rb = tid & 3;
-  if (16 * rb < rows) {
-    uint32_t cw = 0, mw = 0;
+  // phase 2: thread -> (16-row block tid % 8, columns 4 (tid / 8) .. + 3)
+  const int rb = tid & 7, quad = tid >> 3;
+  uint32_t cw[4] = {0, 0, 0, 0}, mw[4] = {0, 0, 0, 0}, sel[4] = {0, 0, 0, 0};
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      float av[4];
-      int fv[4];
-      uint32_t uv[4];
+  for (int c = 0; c < 4; ++c) {
+    uint32_t w[4], key[4][4];
+    const f4_t sc = *reinterpret_cast<const f4_t*>(&sc_s[16 * rb + 4 * c]);
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int row = 16 * rb + 4 * c + i;
-        uv[i] = u_s[row][col];
-        fv[i] = f_s[row][col];
-        av[i] = fabsf((float)((int)uv[i] - 8) * sc_s[row]);   // exact: 3-bit x 11-bit significand
-      }
-      int keep[4];
+    for (int i = 0; i < 4; ++i) w[i] = e_s[pb_word(16 * rb + 4 * c + i, quad)];
 #pragma unroll
-      for (int p = 0; p < 4; ++p) {
-        int rank = 0;
+    for (int i = 0; i < 4; ++i) {
+      // |code - 8| of four columns: below 8 the two's complement of the low three bits (8 for code 0)
+      const uint32_t neg = (~w[i] & 0x08080808u) >> 3;
+      const uint32_t m = ((w[i] & 0x07070707u) ^ ((neg << 3) - neg)) + neg;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          if (q == p) continue;
-          const bool better = av[q] > av[p] || (av[q] == av[p] && (fv[q] > fv[p] || (fv[q] == fv[p] && q < p)));
-          if (better) ++rank;
-        }
-        keep[p] = rank < 2;
-      }
-      int i0 = -1, i1 = -1;
-#pragma unroll
-      for (int p = 0; p < 4; ++p)
-        if (keep[p]) {
-          if (i0 < 0) i0 = p;
-          else i1 = p;
-        }
-      cw |= (uv[i0] << (4 * c)) | (uv[i1] << (16 + 4 * c));
-      mw |= (uint32_t)(i0 | (i1 << 2)) << (4 * c);
-      sel16 |= (uint32_t)((keep[0] & fv[0]) | ((keep[1] & fv[1]) << 1) | ((keep[2] & fv[2]) << 2) |
-                          ((keep[3] & fv[3]) << 3)) << (4 * c);
+      for (int b = 0; b < 4; ++b)
+        key[b][i] = __float_as_uint((float)((m >> (8 * b)) & 0xFFu) * sc[i]) | ((w[i] >> (8 * b)) & 0xFFu);
     }
-    // transposed pack: row k, reduction n; n0 is a multiple of 64, so the 16-row block rb is
-    // word (n0 % 128) / 16 + rb of chunk n0 / 128
-    const int64_t k = k0 + col;
-    const int64_t slotT = packed_slot(k, n0 >> 7, N / 128);
-    codesT[8 * slotT + ((n0 & 127) >> 4) + rb] = cw;
-    metaT[8 * slotT + ((n0 & 127) >> 4) + rb] = (uint16_t)mw;
-  }
-  if (mask_rc) {
-    __syncthreads();
-    if (16 * rb < rows) {
 #pragma unroll
-      for (int i = 0; i < 16; ++i) f_s[16 * rb + i][col] = (sel16 >> i) & 1;
-    }
-    __syncthreads();
-    // write rows of the tile: thread -> (row = tid / 4, 16 bytes at column 16 * (tid % 4))
-    const int row = tid >> 2, w = tid & 3;
-    if (row < rows) {
-      uint32_t v[4];
-#pragma unroll
-      for (int q = 0; q < 4; ++q)
-        v[q] = (uint32_t)f_s[row][16 * w + 4 * q] | ((uint32_t)f_s[row][16 * w + 4 * q + 1] << 8) |
-               ((uint32_t)f_s[row][16 * w + 4 * q + 2] << 16) | ((uint32_t)f_s[row][16 * w + 4 * q + 3] << 24);
-      uint4* dst = reinterpret_cast<uint4*>(mask_rc + (n0 + row) * K + k0 + 16 * w);
-      *dst = make_uint4(v[0], v[1], v[2], v[3]);
+    for (int b = 0; b < 4; ++b) {
+      const uint32_t h0 = max(key[b][0], key[b][1]), l0 = min(key[b][0], key[b][1]);
+      const uint32_t h1 = max(key[b][2], key[b][3]), l1 = min(key[b][2], key[b][3]);
+      const uint32_t first = max(h0, h1), second = max(min(h0, h1), max(l0, l1));
+      // in row order: the larger 3 - n % 4 is the earlier row
+      const uint32_t lo = max(first & 0x3Fu, second & 0x3Fu), hi = min(first & 0x3Fu, second & 0x3Fu);
+      cw[b] |= ((lo & 0xFu) << (4 * c)) | ((hi & 0xFu) << (16 + 4 * c));
+      mw[b] |= ((lo >> 4) | ((hi >> 4) << 2)) << (4 * c);     // each 3 - position: complemented below
+      if constexpr (MASK) {
+        sel[b] |= ((first >> 6) & 1u) << (4 * c + 3 - ((first >> 4) & 3u));
+        sel[b] |= ((second >> 6) & 1u) << (4 * c + 3 - ((second >> 4) & 3u));
+      }
     }
   }
-  // scalesT: the first column tile of each 128-group copies the tile's row scales
-  if ((k0 & 127) == 0 && tid < rows) scalesT[(k0 >> 7) * N + n0 + tid] = scales[packed_slot(n0 + tid, k0 >> 7, K / 128)];
+  // transposed pack: row k, reduction n
+#pragma unroll
+  for (int b = 0; b < 4; ++b) {
+    const int64_t slotT = packed_slot(k0 + 4 * quad + b, nc, N / 128);
+    codesT[8 * slotT + rb] = cw[b];
+    metaT[8 * slotT + rb] = (uint16_t)~mw[b];
+  }
+  if constexpr (MASK) {
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 16; ++i)
+      e_s[pb_word(16 * rb + i, quad)] = ((sel[0] >> i) & 1u) | (((sel[1] >> i) & 1u) << 8) | (((sel[2] >> i) & 1u) << 16) |
+                                        (((sel[3] >> i) & 1u) << 24);
+    __syncthreads();
+    // rows of the tile: thread -> (row tid / 8 + 32 j, 16 bytes at column 16 (tid % 8))
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int row = (tid >> 3) + 32 * j;
+      *reinterpret_cast<u32x4_t*>(mask_rc + (n0 + row) * K + k0 + 16 * (tid & 7)) =
+          *reinterpret_cast<const u32x4_t*>(&e_s[pb_word(row, 4 * (tid & 7))]);
+    }
+  }
 }
 
 // fp16 transpose out[c][r] = in[r][c] of a row-major [R x C] matrix, through a 64 x 64 LDS tile.
@@ -361,15 +363,15 @@ int pack_forward(const float* W, int64_t N, int64_t K, uint8_t* codes, uint8_t* 
   if (hipMalloc(&d_status, sizeof(int)) != hipSuccess) return SLIM_EDEVICE;
   int h_status = 0;
   int rc = SLIM_OK;
-  const int64_t total4 = N * (K / 4);
-  const int64_t blocks = (total4 + kPackThreads - 1) / kPackThreads;
+  const int64_t total16 = N * (K / 16);
+  const int64_t blocks = (total16 + kPackThreads - 1) / kPackThreads;
   do {
     if (hipMemsetAsync(d_status, 0, sizeof(int), s) != hipSuccess) { rc = SLIM_EDEVICE; break; }
     {
       SlimKernelTimer timer("pack", s);
-      SLIM_LAUNCH(timer, k_pack, dim3((unsigned)blocks), dim3(kPackThreads), s, reinterpret_cast<const float4*>(W),
-                  total4, K, reinterpret_cast<uint32_t*>(codes), reinterpret_cast<uint16_t*>(meta), scales,
-                  reinterpret_cast<uint32_t*>(mask), d_status, alpha);
+      SLIM_LAUNCH(timer, k_pack, dim3((unsigned)blocks), dim3(kPackThreads), s,
+                  reinterpret_cast<const u32x4_t*>(W), total16, K / 128, reinterpret_cast<uint32_t*>(codes),
+                  reinterpret_cast<uint16_t*>(meta), scales, reinterpret_cast<u32x4_t*>(mask), d_status, alpha);
     }
     if (hipGetLastError() != hipSuccess) { rc = SLIM_EDEVICE; break; }
     if (hipMemcpyAsync(&h_status, d_status, sizeof(int), hipMemcpyDeviceToHost, s) != hipSuccess ||
@@ -408,9 +410,10 @@ extern "C" int slim_pack_bwd(const uint8_t* codes, const uint8_t* meta, const ui
   do {
     if (hipMemsetAsync(d_status, 0, sizeof(int), s) != hipSuccess) { rc = SLIM_EDEVICE; break; }
     {
-      dim3 grid((unsigned)(K / kBT), (unsigned)((N + kBT - 1) / kBT));
+      dim3 grid((unsigned)(K / kBT), (unsigned)(N / kBT));
       SlimKernelTimer timer("pack_bwd", s);
-      SLIM_LAUNCH(timer, k_pack_bwd, grid, dim3(256), s, reinterpret_cast<const uint32_t*>(codes),
+      auto kernel = mask_rc ? k_pack_bwd<true> : k_pack_bwd<false>;
+      SLIM_LAUNCH(timer, kernel, grid, dim3(256), s, reinterpret_cast<const uint32_t*>(codes),
                   reinterpret_cast<const uint16_t*>(meta), scales, N, K, reinterpret_cast<uint32_t*>(codesT),
                   reinterpret_cast<uint16_t*>(metaT), scalesT, mask_rc, d_status);
     }

@@ -39,6 +39,20 @@ def test_pack_bit_exact_ties_and_signed_zeros():
     _check_pack(_tied(128, 512, 3))
 
 
+def test_pack_half_way_quotients():
+    # magnitudes at (j + 1/2) s and one place to either side, for scales with few and many significant bits
+    # and subnormal ones; the group maximum 7 s makes s the group's scale exactly
+    rng = synth.stream(11, "halfway")
+    s = np.concatenate([np.float16(2.0) ** np.arange(-24, 11, dtype=np.float32), (rng.random(285) * 0.1).astype(np.float32)])
+    s = s.astype(np.float16).astype(np.float32).reshape(320, 1)
+    W = (rng.integers(0, 7, size=(320, 128)).astype(np.float32) + np.float32(0.5)) * s
+    side = rng.integers(-1, 2, size=W.shape)
+    W = np.where(side < 0, np.nextafter(W, np.float32(0)), np.where(side > 0, np.nextafter(W, np.float32(1e9)), W))
+    W[:, 5] = 7 * s[:, 0]
+    W = np.where(rng.random(W.shape) < 0.5, -W, W).astype(np.float32)
+    _check_pack(W)
+
+
 def test_pack_zero_and_tiny_groups():
     W = synth.weights(32, 256, seed=4)
     W[3, :128] = 0.0
@@ -89,6 +103,12 @@ def test_pack_bwd_bit_exact(n, k, tied):
     ref = O.pack_bwd(O.pack(W), n, k)
     for key in ("codesT", "metaT", "scalesT", "mask_rc"):
         assert np.array_equal(b[key], ref[key]), key
+
+
+# one and several 128 x 128 tiles along either side
+@pytest.mark.parametrize("n,k,tied", [(128, 128, True), (384, 128, True), (256, 640, False)])
+def test_pack_bwd_tiles(n, k, tied):
+    test_pack_bwd_bit_exact(n, k, tied)
 
 
 def test_pack_bwd_full_size_sampled_groups():
