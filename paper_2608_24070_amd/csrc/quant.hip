@@ -20,8 +20,8 @@
 
 namespace {
 
-constexpr int kQThreads = 256;
-constexpr int kQMaxBins = 20480;           // 80 KiB of LDS counters: two blocks per CU
+constexpr int kQThreads = 512;
+constexpr int kQMaxBins = 20480;           // 80 KiB of LDS counters
 constexpr int kQHistThreads = 1024;
 constexpr int kQCoarse = 10, kQFine = 20;  // candidates of the two grids
 constexpr int kQSearchThreads = 512;
@@ -36,40 +36,31 @@ k_quant_clear(uint32_t* __restrict__ hist, int bins, uint32_t* __restrict__ amax
   }
 }
 
+// Magnitudes compared as bit patterns (a non-finite one is at least infinity's), four loads in flight per
+// thread: bound by the reading of W (180 MB: 50 us with 2048 blocks of 256 threads, one load each in flight, 34
+// now).
 __global__ void __launch_bounds__(kQThreads)
-k_quant_absmax(const float4* __restrict__ W, int64_t n4, uint32_t* __restrict__ amax_bits, int* __restrict__ status) {
-  float m = 0.f;
-  int bad = 0;
-  for (int64_t i = (int64_t)blockIdx.x * kQThreads + threadIdx.x; i < n4; i += (int64_t)gridDim.x * kQThreads) {
-    const float4 v = W[i];
-    const float w[4] = {v.x, v.y, v.z, v.w};
+k_quant_absmax(const u32x4_t* __restrict__ W, int64_t n4, uint32_t* __restrict__ amax_bits, int* __restrict__ status) {
+  uint32_t m = 0;
+  const int64_t stride = (int64_t)gridDim.x * kQThreads;
+  for (int64_t i = (int64_t)blockIdx.x * kQThreads + threadIdx.x; i < n4; i += 4 * stride) {
+    u32x4_t v[4];
 #pragma unroll
-    for (int p = 0; p < 4; ++p) {
-      if (!__builtin_isfinite(w[p])) bad = 1;
-      m = fmaxf(m, fabsf(w[p]));
-    }
+    for (int j = 0; j < 4; ++j) v[j] = W[i + j * stride < n4 ? i + j * stride : i];
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int p = 0; p < 4; ++p) m = max(m, v[j][p] & 0x7FFFFFFFu);
   }
 #pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
-  bad = __any(bad) ? 1 : 0;
-  __shared__ float wm[kQThreads / 64];
-  __shared__ int wb[kQThreads / 64];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  if (lane == 0) {
-    wm[wave] = m;
-    wb[wave] = bad;
-  }
+  for (int off = 32; off >= 1; off >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, off, 64));
+  __shared__ uint32_t wm[kQThreads / 64];
+  if ((threadIdx.x & 63) == 0) wm[threadIdx.x >> 6] = m;
   __syncthreads();
   if (threadIdx.x == 0) {
-    float bm = wm[0];
-    int bb = wb[0];
-    for (int w = 1; w < kQThreads / 64; ++w) {
-      bm = fmaxf(bm, wm[w]);
-      bb |= wb[w];
-    }
-    // non-negative floats order like their bit patterns
-    atomicMax(amax_bits, __float_as_uint(bm));
-    if (bb) atomicOr(status, 1);
+    for (int w = 1; w < kQThreads / 64; ++w) m = max(m, wm[w]);
+    atomicMax(amax_bits, m);
+    if (m >= 0x7F800000u) atomicOr(status, 1);
   }
 }
 
@@ -86,7 +77,11 @@ __device__ __forceinline__ int bin_of(float a, double bins_d, double amax, doubl
   return b < 0 ? 0 : (b < bins ? b : bins - 1);
 }
 
-// Grid-stride over pairs of float4, both loads issued before the counting.
+// Grid-stride over groups of four float4, every load issued before the counting. A bin comes from fp32
+// arithmetic with the factor bins / amax in two parts: b0 + frac is a bins / amax (at most 2^15) to within
+// 2^-24, and where frac lies 2^-20 or further from both 0 and 1, b0 is the bin; only the other few magnitudes
+// (and all of them for a factor far from fp32's middle range) take the float64 bin_of, which alone kept the
+// float64 units busy for most of the time: 180 MB took 46 us with it, two loads in flight and 512 blocks, 35 now.
 __global__ void __launch_bounds__(kQHistThreads)
 k_quant_hist(const float4* __restrict__ W, int64_t n4, int bins, const uint32_t* __restrict__ amax_bits,
              uint32_t* __restrict__ hist) {
@@ -97,21 +92,32 @@ k_quant_hist(const float4* __restrict__ W, int64_t n4, int bins, const uint32_t*
   // all-zero weights: every magnitude in bin 0; an infinite maximum (reported by the call): likewise
   const bool binned = amax > 0.0 && amax < INFINITY;
   const double bins_d = (double)bins, inv = binned ? 1.0 / amax : 0.0;
+  const double fac = bins_d * inv;
+  const bool fast = fac > 0x1p-60 && fac < 0x1p60;     // NaN parts otherwise: every magnitude takes bin_of
+  const float fh = fast ? (float)fac : __builtin_nanf(""), fl = (float)(fac - (double)fh);
   auto count4 = [&](const float4 v) {
     const float w[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
     for (int p = 0; p < 4; ++p) {
-      const int b = binned ? bin_of(fabsf(w[p]), bins_d, amax, inv, bins) : 0;
+      const float a = fabsf(w[p]);
+      const float b0 = floorf(a * fh);
+      const float frac = fmaf(a, fl, fmaf(a, fh, -b0));
+      int b = (int)b0;
+      if (!(fabsf(frac - 0.5f) < 0.5f - 0x1p-20f)) {     // also where frac is NaN
+        b = 0;
+        if (binned && a != 0.f) b = bin_of(a, bins_d, amax, inv, bins);
+      }
       atomicAdd(&hs[b], 1u);
     }
   };
   const int64_t stride = (int64_t)gridDim.x * kQHistThreads;
-  for (int64_t i = (int64_t)blockIdx.x * kQHistThreads + threadIdx.x; i < n4; i += 2 * stride) {
-    const float4 v0 = W[i];
-    const bool two = i + stride < n4;
-    const float4 v1 = two ? W[i + stride] : make_float4(0.f, 0.f, 0.f, 0.f);
-    count4(v0);
-    if (two) count4(v1);
+  for (int64_t i = (int64_t)blockIdx.x * kQHistThreads + threadIdx.x; i < n4; i += 4 * stride) {
+    float4 v[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) v[j] = W[i + j * stride < n4 ? i + j * stride : i];
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      if (i + j * stride < n4) count4(v[j]);
   }
   __syncthreads();
   for (int b = threadIdx.x; b < bins; b += kQHistThreads) {
@@ -279,9 +285,9 @@ extern "C" int slim_quant_search(const float* W, int64_t count, int bits, int64_
   int h_status = 0, rc = SLIM_OK;
   const int64_t n4 = count / 4;
   int64_t grid = (n4 + kQThreads - 1) / kQThreads;
-  if (grid > 2048) grid = 2048;      // grid-stride: eight blocks per CU
+  if (grid > 256) grid = 256;        // grid-stride, one block per CU: 34 us for 180 MB, 36 with 512, 39 with 1024
   int64_t hgrid = (n4 + kQHistThreads - 1) / kQHistThreads;
-  if (hgrid > 512) hgrid = 512;      // two blocks per CU
+  if (hgrid > 256) hgrid = 256;      // one block per CU, as every block merges its bins: 35 us, 43 with 512
   do {
     {
       SlimKernelTimer timer("quant_clear", s);
@@ -291,7 +297,7 @@ extern "C" int slim_quant_search(const float* W, int64_t count, int bits, int64_
     {
       SlimKernelTimer timer("quant_absmax", s);
       SLIM_LAUNCH(timer, k_quant_absmax, dim3((unsigned)grid), dim3(kQThreads), s,
-                  reinterpret_cast<const float4*>(W), n4, d_amax, d_status);
+                  reinterpret_cast<const u32x4_t*>(W), n4, d_amax, d_status);
     }
     {
       SlimKernelTimer timer("quant_hist", s);

@@ -64,6 +64,17 @@ def test_search_bins_at_edges():
     _check_search(W.reshape(16, 128), bins=600)
 
 
+# bins by the fp32 product and, where bins / max |w| leaves its range, by the float64 one; whole and part groups
+# of four loads of the 256 blocks
+@pytest.mark.parametrize("scale", [1.0, 1e-14, 1e-17, 1e-30, 1e18, 1e24])
+@pytest.mark.parametrize("n,k", [(16, 128), (1040, 3968)])
+def test_search_scales(n, k, scale):
+    print(f"quant search n={n} k={k} scale={scale}", flush=True)
+    W = _weights(n, k, 3, 0) * np.float32(scale)
+    W[:, ::7] = 0
+    _check_search(W.astype(np.float32))
+
+
 def test_search_full_size_70b():
     n, k = 28672, 8192
     print(f"quant search full size n={n} k={k}", flush=True)
