@@ -10,7 +10,8 @@
 //                    one weight tile, dense (v_mfma_f32_32x32x16_f16) or sparse
 //                    (v_smfmac_f32_32x32x32_f16, half the MFMA issue for the same K); both write
 //                    the same 32 x 32 accumulator layout, so a tile row may mix them freely
-//   k_hybrid_reduce  the split partials of small-M calls, summed in split order
+//   k_hybrid_few     up to 64 rows: 16 or 32 rows of Y^T per block, K shared by its waves
+//   k_hybrid_reduce  the split partials of the GEMM, summed in a fixed order
 #include <new>
 
 #include "slim_device.h"
@@ -375,30 +376,220 @@ k_hybrid_gemm(HybridArgs g) {
   }
 }
 
+// ------------------------------------------------------------------------------------- few rows
+// M <= 16 MF: bound by the reading of the weights. A block takes 16 RF rows of one tile row with W waves
+// that share K chunk by chunk (wave w takes chunks w, w + W, ...), and adds their sums through LDS in wave order:
+// no partials in memory and no second launch. A wave loads its weights and its activations (from the L2) itself,
+// two chunks in flight, X and dense weights as whole rows of a chunk (256 bytes); it turns them through its own
+// LDS, without a barrier, into the MFMA's operand layout, which loaded directly is 64-byte pieces of 16 rows
+// and reads every 128-byte line twice (16 x 11008 x 4096: 20.3 us; 13.7 now, 62 MB at 4.5 TB/s; 25.0 in
+// 128-column tiles and partials). Dense chunks run four v_mfma_f32_16x16x32_f16, 2:4 ones two
+// v_smfmac_f32_16x16x64_f16 per fragment, on the same X registers: lane (i, g = lane / 16) holds positions
+// 8 g .. + 7 of each 32 of row i. 2:4 values (64-byte rows) and index words lie as the lanes take them.
+template <int RF, int MF, int W>
+__global__ void __launch_bounds__(64 * W)
+k_hybrid_few(HybridArgs g) {
+  // two buffers of 4 KiB per wave, 16 rows of 256 bytes each; the sums at the end
+  static_assert(RF * MF <= 8, "a wave's sums fit its two buffers");
+  __shared__ u32x4_t stage[W][2][256];
+  f4_t* part = reinterpret_cast<f4_t*>(&stage[0][0][0]);
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int li = lane & 15, lg = lane >> 4;
+  const int64_t n0 = (int64_t)blockIdx.x * 16 * RF;
+  const int chunks = (int)(g.K / kHT);
+  const uint64_t* info = g.info + (n0 / kHT) * chunks;
+  const int rt = (int)(n0 % kHT), r0 = rt + li;
+  const rsrc_t rw = make_rsrc(g.payload, g.payload_bytes), rx = make_rsrc(g.X, g.M * g.K * 2);
+  // whole rows of 256 bytes: load i of a fragment takes row 4 i + lg, 16-byte slot li (X rows past M read as
+  // zero); the wave's LDS keeps slot s of row r at s ^ r, so neither the writes nor the reads below, lane (li, lg)
+  // taking slot 4 t + lg of row li, conflict
+  uint32_t xo[MF][4];
+#pragma unroll
+  for (int m = 0; m < MF; ++m)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) xo[m][i] = (uint32_t)(16 * m + 4 * i + lg) * (uint32_t)g.K * 2u + 16u * (uint32_t)li;
+  const uint32_t od = (uint32_t)(rt + lg) * 256u + 16u * (uint32_t)li, os = (uint32_t)r0 * 64u + 16u * (uint32_t)lg,
+                 oi = 8192u + (uint32_t)r0 * 8u + 2u * (uint32_t)lg;
+  uint32_t wr[4], rd[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    wr[i] = (uint32_t)(16 * (4 * i + lg) + (li ^ (4 * i + lg)));
+    rd[i] = (uint32_t)(16 * li + ((4 * i + lg) ^ li));
+  }
+  u32x4_t (*mine)[256] = stage[wave];
+  struct Set {
+    u32x4_t w[RF][4], x[MF][4];
+    uint32_t i[RF][2];
+    bool sparse;
+  };
+  auto load16 = [](const rsrc_t& r, uint32_t off, uint32_t base) {
+    return __builtin_bit_cast(u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(r, off, base, 0));
+  };
+  auto load = [&](Set& S, int c) {
+    const uint64_t ti = info[c];
+    const uint32_t toff = (uint32_t)(ti & ~kHSparseBit);
+    S.sparse = (ti & kHSparseBit) != 0;
+    if (S.sparse) {
+#pragma unroll
+      for (int f = 0; f < RF; ++f)
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+          S.w[f][t] = load16(rw, os + 1024u * f, toff + (uint32_t)(kHSparse / 2) * t);
+          S.i[f][t] = __builtin_amdgcn_raw_buffer_load_b16(rw, oi + 128u * f, toff + (uint32_t)(kHSparse / 2) * t, 0);
+        }
+    } else {
+#pragma unroll
+      for (int f = 0; f < RF; ++f)
+#pragma unroll
+        for (int t = 0; t < 4; ++t) S.w[f][t] = load16(rw, od + 4096u * f + 1024u * t, toff);
+    }
+#pragma unroll
+    for (int m = 0; m < MF; ++m)
+#pragma unroll
+      for (int t = 0; t < 4; ++t) S.x[m][t] = load16(rx, xo[m][t], (uint32_t)c * 256u);
+  };
+  // of the wave's even and odd chunks, where the registers allow it: shorter chains of roundings
+  constexpr int kAcc = W > 4 && MF < 4 ? 2 : 1;
+  f4_t acc[kAcc][RF][MF];
+#pragma unroll
+  for (int a = 0; a < kAcc; ++a)
+#pragma unroll
+    for (int f = 0; f < RF; ++f)
+#pragma unroll
+      for (int m = 0; m < MF; ++m) acc[a][f][m] = f4_t{0.f, 0.f, 0.f, 0.f};
+  auto h8 = [](u32x4_t v) { return __builtin_bit_cast(h8_t, v); };
+  auto compute = [&](Set& S, f4_t (&acc)[RF][MF]) {
+    auto turn = [&](u32x4_t (&v)[4], u32x4_t* buf) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) buf[wr[i]] = v[i];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) v[i] = buf[rd[i]];
+    };
+#pragma unroll
+    for (int m = 0; m < MF; ++m) turn(S.x[m], mine[m & 1]);
+    if (!S.sparse)
+#pragma unroll
+      for (int f = 0; f < RF; ++f) turn(S.w[f], mine[(MF + f) & 1]);
+    if (S.sparse) {
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int f = 0; f < RF; ++f)
+#pragma unroll
+          for (int m = 0; m < MF; ++m)
+            acc[f][m] = smfmac16(h8(S.w[f][t]), cat16(h8(S.x[m][2 * t]), h8(S.x[m][2 * t + 1])), acc[f][m], (int)S.i[f][t], 0);
+    } else {
+#pragma unroll
+      for (int t = 0; t < 4; ++t)
+#pragma unroll
+        for (int f = 0; f < RF; ++f)
+#pragma unroll
+          for (int m = 0; m < MF; ++m) acc[f][m] = mfma16(h8(S.w[f][t]), h8(S.x[m][t]), acc[f][m]);
+    }
+  };
+  Set A, B;
+  int c = wave;
+  if (c < chunks) {
+    load(A, c);
+    while (true) {
+      if (c + W < chunks) load(B, c + W);
+      compute(A, acc[0]);
+      if (c + W >= chunks) break;
+      if (c + 2 * W < chunks) load(A, c + 2 * W);
+      compute(B, acc[kAcc - 1]);
+      if (c + 2 * W >= chunks) break;
+      c += 2 * W;
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int f = 0; f < RF; ++f)
+#pragma unroll
+    for (int m = 0; m < MF; ++m) part[(wave * RF * MF + f * MF + m) * 64 + lane] = kAcc > 1 ? acc[0][f][m] + acc[kAcc - 1][f][m] : acc[0][f][m];
+  __syncthreads();
+  // D[i][j] of a 16 x 16 fragment: lane j + 16 (i / 4), element i % 4
+  for (int t = tid; t < 64 * RF * MF; t += 64 * W) {
+    const int fr = t >> 6;
+    f4_t o = part[fr * 64 + lane];
+#pragma unroll
+    for (int w = 1; w < W; ++w) o += part[(w * RF * MF + fr) * 64 + lane];
+    const int64_t m = 16 * (fr % MF) + li, nn = n0 + 16 * (fr / MF) + 4 * lg;
+    if (m < g.M) *reinterpret_cast<f4_t*>(g.out + m * g.N + nn) = o;
+  }
+}
+
+// Sums of the split partials, in an order fixed by the split count: 64 outputs (of four values) per block, the
+// splits over four groups of threads with four loads in flight each, the groups' sums added through LDS. One
+// thread per output walking all splits waited for every load in turn (112 splits: 28 us).
 __global__ void __launch_bounds__(kHThreads)
 k_hybrid_reduce(const float* __restrict__ part, int splits, int64_t count4, float* __restrict__ Y) {
-  const int64_t i = (int64_t)blockIdx.x * kHThreads + threadIdx.x;
-  if (i >= count4) return;
-  const f4_t* p = reinterpret_cast<const f4_t*>(part);
-  f4_t s = p[i];
-  for (int z = 1; z < splits; ++z) s += p[(int64_t)z * count4 + i];
-  reinterpret_cast<f4_t*>(Y)[i] = s;
+  __shared__ f4_t sums[3][64];
+  const int lane = threadIdx.x & 63, grp = threadIdx.x >> 6;
+  const int64_t i = (int64_t)blockIdx.x * 64 + lane;
+  const f4_t* p = reinterpret_cast<const f4_t*>(part) + (i < count4 ? i : count4 - 1);
+  f4_t s = f4_t{0.f, 0.f, 0.f, 0.f};
+  int z = grp;
+  for (; z + 12 < splits; z += 16) {
+    const f4_t v0 = p[z * count4], v1 = p[(z + 4) * count4], v2 = p[(z + 8) * count4], v3 = p[(z + 12) * count4];
+    s += (v0 + v1) + (v2 + v3);
+  }
+  for (; z < splits; z += 4) s += p[z * count4];
+  if (grp > 0) sums[grp - 1][lane] = s;
+  __syncthreads();
+  if (grp == 0 && i < count4) reinterpret_cast<f4_t*>(Y)[i] = (s + sums[0][lane]) + (sums[1][lane] + sums[2][lane]);
+}
+
+// Rows served by k_hybrid_few. Its weights are read once whatever M is, and X once per row block, so it is the
+// faster one while X is small beside them; a wave's chunks are a serial chain of about 1 us each.
+//   M <= 16: always (16 x 11008 x 4096: 13.7 us against 20.8, 16 x 1024 x 1024 3.0 against 7.8, 14336 x 14336 59
+//     against 72; 512 x 14336 level at 12; the sums' chains are no longer than in the GEMM's splits)
+//   M <= 32: unless few row blocks each have a long chain (32 x 512 x 14336: 18.7 against 13.9; 4096 x 11008
+//     17.5 against 22.4, 14336 x 14336 72 against 74)
+//   M <= 64: up to 4096 x 4096 (64 rows: 12.7 against 16.7; 11008 x 4096: 30.4 against 27.8)
+bool hybrid_few(int64_t M, int64_t N, int64_t K) {
+  if (M <= 16) return true;
+  if (M <= 32) return N > 2048 || K <= 8192;
+  return M <= 64 && N <= 4096 && K <= 4096;
 }
 
 struct HybridPlan {
+  bool few;
   int64_t tiles, splits, chunks_per_split;
   size_t ws;
 };
 
+// Splits of K: the count of least estimated time. A block takes t0 = 4.5 us and 2 us per chunk (fitted at 64
+// rows of 4096 x 4096 in 1 to 32 splits, 65 to 13 us a launch; with 256 blocks at work a chunk's 45 KB each
+// make 5.8 TB/s), blocks run 256 at a time with the last split's shorter ones last, and the partials cost
+// the reduction's launch, 3 us, and their writing and reading at 7 TB/s.
 HybridPlan hybrid_plan(int64_t M, int64_t N, int64_t K) {
   HybridPlan p{};
+  p.few = hybrid_few(M, N, K);
+  if (p.few) {
+    p.splits = 1;
+    return p;
+  }
   const int64_t chunks = K / kHT;
   p.tiles = ((N + kHRows - 1) / kHRows) * ((M + kHT - 1) / kHT);
-  int64_t s = 1;
-  if (p.tiles < 256) s = (512 + p.tiles - 1) / p.tiles;          // at least ~512 blocks
-  if (s > chunks) s = chunks;
-  p.chunks_per_split = (chunks + s - 1) / s;
-  p.splits = (chunks + p.chunks_per_split - 1) / p.chunks_per_split;
+  int64_t most = p.tiles < 256 ? (512 + p.tiles - 1) / p.tiles : 1;     // no more than two rounds of blocks
+  if (most > chunks) most = chunks;
+  double best = 0;
+  for (int64_t want = 1; want <= most; ++want) {
+    const int64_t cps = (chunks + want - 1) / want, s = (chunks + cps - 1) / cps;
+    if (s < want) continue;
+    const double full = 4.5 + 2.0 * cps, last = 4.5 + 2.0 * (chunks - (s - 1) * cps);
+    const int64_t nfull = p.tiles * (s - 1), busy = nfull % 256, idle = 256 - busy;
+    // whole rounds, then the busy blocks' end or the last split's, in as many rounds as the idle CUs need
+    double t = full * (double)(nfull / 256);
+    const double ends = last * (double)((p.tiles + idle - 1) / idle), both = (busy ? full : 0) + last * (double)((p.tiles + 255) / 256);
+    t += busy && ends < full ? full : (ends < both ? ends : both);
+    if (s > 1) t += 3.0 + (double)s * M * N * 8 / 7e6;
+    if (want == 1 || t < best) {
+      best = t;
+      p.splits = s;
+      p.chunks_per_split = cps;
+    }
+  }
   p.ws = p.splits > 1 ? (size_t)p.splits * M * N * sizeof(float) : 0;
   return p;
 }
@@ -486,6 +677,29 @@ extern "C" int slim_linear_hybrid(const void* X, int64_t M, int64_t N, int64_t K
   if (p.splits > 1 && (!ws || ws_bytes < p.ws)) return SLIM_EWORKSPACE;
   if (p.splits > 1 && !slim_aligned16(ws)) return SLIM_EALIGN;
   hipStream_t s = (hipStream_t)stream;
+  if (p.few) {
+    const HybridArgs a{static_cast<const uint16_t*>(X), tile_info, payload, Y, M, N, K, (int64_t)payload_bytes, 0};
+    SlimKernelTimer timer("hybrid_few", s);
+    auto go = [&](auto kernel, int rows, int waves) {
+      SLIM_LAUNCH(timer, kernel, dim3((unsigned)(N / rows)), dim3((unsigned)(64 * waves)), s, a);
+    };
+    // up to 4096 rows a row block has a CU to itself and takes more waves; from 12288 on, 32-row blocks still
+    // give every CU work and read X half as often (16 x 14336 x 14336: 59 us, 69 with 16; 16 x 11008 x
+    // 4096: 15.6, 13.7 with 16)
+    const bool low = N <= 4096, high = N >= 12288;
+    if (M <= 16) {
+      if (low) go(k_hybrid_few<1, 1, 16>, 16, 16);
+      else if (high) go(k_hybrid_few<2, 1, 8>, 32, 8);
+      else go(k_hybrid_few<1, 1, 8>, 16, 8);
+    } else if (M <= 32) {
+      if (low) go(k_hybrid_few<1, 2, 8>, 16, 8);
+      else if (high) go(k_hybrid_few<2, 2, 8>, 32, 8);
+      else go(k_hybrid_few<1, 2, 4>, 16, 4);
+    } else {
+      go(k_hybrid_few<1, 4, 8>, 16, 8);
+    }
+    return hipGetLastError() == hipSuccess ? SLIM_OK : SLIM_EDEVICE;
+  }
   HybridArgs a{static_cast<const uint16_t*>(X), tile_info, payload, p.splits > 1 ? static_cast<float*>(ws) : Y,
                M, N, K, (int64_t)payload_bytes, (int)p.chunks_per_split};
   {
@@ -497,7 +711,7 @@ extern "C" int slim_linear_hybrid(const void* X, int64_t M, int64_t N, int64_t K
   if (p.splits > 1) {
     const int64_t count4 = M * N / 4;
     SlimKernelTimer timer("hybrid_reduce", s);
-    SLIM_LAUNCH(timer, k_hybrid_reduce, dim3((unsigned)((count4 + kHThreads - 1) / kHThreads)), dim3(kHThreads), s,
+    SLIM_LAUNCH(timer, k_hybrid_reduce, dim3((unsigned)((count4 + 63) / 64)), dim3(kHThreads), s,
                 (const float*)static_cast<float*>(ws), (int)p.splits, count4, Y);
   }
   return hipGetLastError() == hipSuccess ? SLIM_OK : SLIM_EDEVICE;

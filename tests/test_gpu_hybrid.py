@@ -78,6 +78,34 @@ def test_linear_odd_tile_rows(n, k, m):
     _check_product(Y, X, P.hybrid_weight(W, kinds))
 
 
+# The kernel for few rows: each of its row counts' edges, its three row-block shapes (N up to 4096, up to 12160,
+# beyond), chunk counts below, at and past one and two per wave, an odd last row of tiles.
+@pytest.mark.parametrize("m", [1, 15, 16, 17, 32, 33, 64])
+@pytest.mark.parametrize("n,k,frac", [(128, 128, 0.5), (1152, 1152, 0.0), (4096, 2176, 0.7), (4224, 4224, 0.6),
+                                      (12288, 640, 0.5)])
+def test_linear_few_rows(n, k, m, frac):
+    print(f"hybrid few n={n} k={k} m={m} frac={frac}", flush=True)
+    W = _w(n, k, 6)
+    kinds = _kinds(n, k, 6, frac)
+    X = _x(m, k, 6)
+    p = slim.pack_hybrid(dev(W), kinds)
+    Y = host(slim.linear_hybrid(dev(X), p))
+    _check_product(Y, X, P.hybrid_weight(W, kinds))
+
+
+# Split counts of the tile GEMM and its reduction: one, a few, and one per chunk; a shorter last split
+@pytest.mark.parametrize("m,n,k", [(32, 512, 14336), (65, 256, 4224), (130, 4096, 4096), (1000, 2048, 1408), (2048, 4096, 256)])
+def test_linear_splits(m, n, k):
+    print(f"hybrid splits m={m} n={n} k={k}", flush=True)
+    W = _w(n, k, 7)
+    kinds = _kinds(n, k, 7, 0.6)
+    X = _x(m, k, 7)
+    p = slim.pack_hybrid(dev(W), kinds)
+    Y = host(slim.linear_hybrid(dev(X), p))
+    rows = np.arange(m) if m <= 130 else np.sort(synth.stream(7, "ghyb/rows").choice(m, size=64, replace=False))
+    _check_product(Y, X[rows], P.hybrid_weight(W, kinds), rows=rows)
+
+
 @pytest.mark.parametrize("m", [16, 2048])
 def test_llama7b_gate_proj_full_size(m):
     # 11008 x 4096 at 35% sparsity (70% of the tiles 2:4), sampled rows of Y
