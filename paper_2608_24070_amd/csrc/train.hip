@@ -68,21 +68,24 @@ k_pack16(const float4* __restrict__ W, int64_t n16, u32x4_t* __restrict__ vals, 
 
 // ----------------------------------------------------------------------------- pack16_t
 // Block = 128 rows (n) x 128 columns (k). Phase 1 expands the value pack of the tile into LDS (fp16
-// bits, 0 where M^R drops, and the M^R bit), each thread 16 columns of four rows with 16-byte LDS
-// writes; phase 2 gives each thread a 16-row block nb and a column k, keeps the top two of each
-// aligned 4-row group by (|v| desc, M^R bit desc, n asc) and writes 8 values (16 B) of valsT and
-// one metaT half-word. A tile row is one whole 128-byte line of the value pack, and the eight
-// 16-row blocks of one column go to eight consecutive threads, so every load and store moves whole
-// lines. LDS columns are XOR-swizzled by the 16-row block (values by 8 nb, flags by 16 nb), so the
-// phase-2 reads of one wave fall in distinct banks. A last partial tile (64 rows or 64 columns) is
-// loaded from clamped addresses and stores only its own part.
+// bits, 0 where M^R drops, and the M^R bits, 16 columns to a half-word), each thread 16 columns of four rows with
+// 16-byte LDS writes; phase 2 gives each thread a 16-row block nb and two columns k, one LDS word per row, keeps the
+// top two of each aligned 4-row group by (|v| desc, M^R bit desc, n asc) and writes 8 values (16 B) of valsT and
+// one metaT half-word per column. One integer per entry orders a group and carries the value (magnitude, M^R bit,
+// 3 - n % 4, sign), so the top two are a max / min network. A tile row is one whole 128-byte line of the value
+// pack, and the eight 16-row blocks of one column go to eight consecutive threads, so every load and store moves
+// whole lines. LDS words are XOR-swizzled by 8 nb and the M^R half-words padded by 16 bytes per 16 rows, so the phase-2
+// reads of one wave fall in distinct banks. A last partial tile (64 rows or 64 columns) is
+// loaded from clamped addresses and stores only its own part. Bound by memory and the two phases' latency
+// (28672 x 8192, 528 MB: 168 us with single columns, a byte per M^R bit and ranks by comparison; 158 now).
 constexpr int kTTn = 128, kTTk = 128;
 
 __global__ void __launch_bounds__(256)
 k_pack16_t(const uint16_t* __restrict__ vals, const uint8_t* __restrict__ meta, int64_t N, int64_t K,
            u32x4_t* __restrict__ valsT, uint16_t* __restrict__ metaT) {
-  __shared__ __attribute__((aligned(16))) uint16_t v_s[kTTn][kTTk];
-  __shared__ __attribute__((aligned(16))) uint8_t f_s[kTTn][kTTk];
+  __shared__ __attribute__((aligned(16))) uint32_t v_s[kTTn][kTTk / 2];
+  __shared__ uint16_t f_s[(kTTn + kTTn / 16) * 8];
+  auto fbits = [&](int row, int w) -> uint16_t& { return f_s[8 * (row + (row >> 4)) + w]; };
   const int tid = threadIdx.x;
   const int64_t k0 = (int64_t)blockIdx.x * kTTk, n0 = (int64_t)blockIdx.y * kTTn;
   const int rows = N - n0 < kTTn ? (int)(N - n0) : kTTn;   // 64 or 128
@@ -103,7 +106,7 @@ k_pack16_t(const uint16_t* __restrict__ vals, const uint8_t* __restrict__ meta, 
   for (int j = 0; j < 4; ++j) {
     const int row = (tid >> 3) + 32 * j;
     const int nb = (row >> 4) & 7;
-    uint32_t vd[8], fd[4];
+    uint32_t vd[8], fd = 0;
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
       const uint32_t i0 = (mws[j] >> (4 * c)) & 3u, i1 = (mws[j] >> (4 * c + 2)) & 3u;
@@ -113,54 +116,55 @@ k_pack16_t(const uint16_t* __restrict__ vals, const uint8_t* __restrict__ meta, 
       for (int p = 0; p < 4; ++p) e[p] = (uint32_t)p == i0 ? lo : ((uint32_t)p == i1 ? hi : 0u);
       vd[2 * c] = e[0] | (e[1] << 16);
       vd[2 * c + 1] = e[2] | (e[3] << 16);
-      fd[c] = (1u << (8 * i0)) | (1u << (8 * i1));
+      fd |= ((1u << i0) | (1u << i1)) << (4 * c);
     }
     if (row < rows && 16 * w < cols) {
-      *reinterpret_cast<u32x4_t*>(&v_s[row][(16 * w) ^ (8 * nb)]) = u32x4_t{vd[0], vd[1], vd[2], vd[3]};
-      *reinterpret_cast<u32x4_t*>(&v_s[row][(16 * w + 8) ^ (8 * nb)]) = u32x4_t{vd[4], vd[5], vd[6], vd[7]};
-      *reinterpret_cast<u32x4_t*>(&f_s[row][(16 * w) ^ (16 * nb)]) = u32x4_t{fd[0], fd[1], fd[2], fd[3]};
+      *reinterpret_cast<u32x4_t*>(&v_s[row][(8 * w) ^ (8 * nb)]) = u32x4_t{vd[0], vd[1], vd[2], vd[3]};
+      *reinterpret_cast<u32x4_t*>(&v_s[row][(8 * w + 4) ^ (8 * nb)]) = u32x4_t{vd[4], vd[5], vd[6], vd[7]};
+      fbits(row, w) = (uint16_t)fd;
     }
   }
   __syncthreads();
-  // thread -> (16-row block tid % 8, column tid / 8 + 32 j)
+  // thread -> (16-row block tid % 8, columns 2 (tid / 8 + 32 j) and the next)
   const int blk = tid & 7;
   if (16 * blk >= rows) return;
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const int col = (tid >> 3) + 32 * j;
-    if (col >= cols) break;
-    uint32_t hv[4], mw = 0;
+  for (int j = 0; j < 2; ++j) {
+    const int pair = (tid >> 3) + 32 * j;
+    if (2 * pair >= cols) break;
+    u32x4_t hv[2];
+    uint32_t mw[2] = {0, 0};
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
-      const int r0 = 16 * blk + 4 * c;
       // key: fp16 magnitude (finite values order as their bit patterns), then the M^R bit, then
-      // the lower row; distinct within a group, so q comes before p exactly when key[q] > key[p]
-      uint32_t key[4], bits[4];
+      // the lower row (distinct within a group), then the sign
+      uint32_t key[2][4];
 #pragma unroll
       for (int p = 0; p < 4; ++p) {
-        bits[p] = v_s[r0 + p][col ^ (8 * blk)];
-        key[p] = ((bits[p] & 0x7FFFu) << 3) | ((uint32_t)f_s[r0 + p][col ^ (16 * blk)] << 2) | (uint32_t)(3 - p);
+        const int row = 16 * blk + 4 * c + p;
+        const uint32_t v = v_s[row][pair ^ (8 * blk)];
+        const uint32_t f = (uint32_t)fbits(row, pair >> 3) >> (2 * (pair & 7));
+        key[0][p] = ((v & 0x7FFFu) << 4) | ((f & 1u) << 3) | (uint32_t)((3 - p) << 1) | ((v >> 15) & 1u);
+        key[1][p] = ((v >> 12) & 0x7FFF0u) | ((f & 2u) << 2) | (uint32_t)((3 - p) << 1) | (v >> 31);
       }
-      // keep[p]: fewer than two entries come before p; exactly two are kept, so the first kept is
-      // among 0..2 and the last among 1..3 (selects, no branches)
-      bool keep[4];
 #pragma unroll
-      for (int p = 0; p < 4; ++p) {
-        uint32_t rank = 0;
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-          if (q != p) rank += key[q] > key[p] ? 1u : 0u;
-        keep[p] = rank < 2;
+      for (int b = 0; b < 2; ++b) {
+        const uint32_t h0 = max(key[b][0], key[b][1]), l0 = min(key[b][0], key[b][1]);
+        const uint32_t h1 = max(key[b][2], key[b][3]), l1 = min(key[b][2], key[b][3]);
+        const uint32_t first = max(h0, h1), second = max(min(h0, h1), max(l0, l1));
+        // in row order: the larger 3 - n % 4 is the earlier row
+        const bool fwd = (first & 6u) > (second & 6u);
+        const uint32_t lo = fwd ? first : second, hi = fwd ? second : first;
+        hv[b][c] = (lo >> 4) | ((lo & 1u) << 15) | ((hi << 12) & 0x7FFF0000u) | (hi << 31);
+        mw[b] |= (((lo >> 1) & 3u) | ((hi << 1) & 0xCu)) << (4 * c);     // each 3 - position: complemented below
       }
-      const uint32_t i0 = keep[0] ? 0u : (keep[1] ? 1u : 2u), i1 = keep[3] ? 3u : (keep[2] ? 2u : 1u);
-      const uint32_t b0 = keep[0] ? bits[0] : (keep[1] ? bits[1] : bits[2]);
-      const uint32_t b1 = keep[3] ? bits[3] : (keep[2] ? bits[2] : bits[1]);
-      hv[c] = b0 | (b1 << 16);
-      mw |= (i0 | (i1 << 2)) << (4 * c);
     }
-    const int64_t k = k0 + col, nb = n0 / 16 + blk;       // 16-row block along n
-    valsT[k * (N / 16) + nb] = u32x4_t{hv[0], hv[1], hv[2], hv[3]};
-    metaT[k * (N / 16) + nb] = (uint16_t)mw;
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+      const int64_t k = k0 + 2 * pair + b, nb = n0 / 16 + blk;       // 16-row block along n
+      valsT[k * (N / 16) + nb] = hv[b];
+      metaT[k * (N / 16) + nb] = (uint16_t)~mw[b];
+    }
   }
 }
 
