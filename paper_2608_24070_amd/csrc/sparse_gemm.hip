@@ -316,10 +316,11 @@ SLIM_DEV void decode_sparse_range(const LayerArgs& a, int s, int64_t rt0, int64_
 // ============================================================ small-M: adapter first-product units
 // tm[m, j] = sum_red act[m, red] Q[j, red]. Unit = 16 adapter columns x 4 parts of ad_sub slices
 // of SLIM_DECODE_AD_SLICE (128) reduction positions: wave w takes part w (more than one slice when
-// the reduction is long, so that there are at most about 8 splits), reading both operands from memory as
-// whole 256-byte rows of a slice (a 4-bit factor's 64 bytes in one load) and turning them in LDS: loaded as the
-// MFMA takes them, 64 (16) bytes of each row at a time, every line was visited twice (eight times); 16 x 5120 x
-// 13824 with 4-bit adapters of rank 512 takes 19.4 us in place of 20.3.
+// the reduction is long, so that there are at most about 8 splits), reading both operands straight
+// from global memory as the MFMA takes them, 64 bytes of each row at a time. With 4-bit factors that would be
+// 16 bytes of each row, eight visits to a line: the slice's 16 rows of 64 bytes come in one load there, and the
+// activations as whole rows of 256 bytes, both turned in LDS (16 x 5120 x 13824, rank 512: 20.6 -> 19.65
+// us; fp16 factors were 1 to 2 % slower turned than straight: 1 x 28672 x 8192 33.1 -> 33.65).
 // The four parts are added in LDS in part order, and the last unit of a column block to finish
 // sums the units' partials in split order. The partial a unit hands over is one 16 x 16
 // fragment per 16 activation rows (1 KB), which keeps the last unit's loads few.
@@ -350,8 +351,8 @@ SLIM_DEV void decode_adapter_unit(const LayerArgs& a, int64_t v, f4_t* red_lds) 
   // codes per step; the round lies in one 128-group (one scale).
   const int64_t ngk = (a.red + 127) / 128;
   const rsrc_t rq4 = make_rsrc(a.q4, a.r * a.red / 2);
-  // The wave's own 4 KiB per fragment of the block's LDS, 16 rows of 256 bytes, slot s of row i at s ^ i: rows
-  // come from memory whole (load i takes row 4 i + g, 16-byte slot lane % 16) and leave as the MFMA takes them
+  // (4-bit factors) The wave's own 4 KiB per fragment of the block's LDS, 16 rows of 256 bytes, slot s of row i
+  // at s ^ i: rows come from memory whole (load i takes row 4 i + g, 16-byte slot lane % 16) and leave as the MFMA takes them
   // (step t, lane (i, g): slot 4 t + g of row i); DS operations of a wave run in order, so there is no barrier.
   u32x4_t* const mine = reinterpret_cast<u32x4_t*>(red_lds) + wave * FM * 256;
   const int li = lane & 15;
@@ -368,27 +369,26 @@ SLIM_DEV void decode_adapter_unit(const LayerArgs& a, int64_t v, f4_t* red_lds) 
     const int64_t rs = r0 + (int64_t)sub * kAdSlice;
     u32x4_t aq[kSteps][FM], bq[kSteps];
     uint32_t qw[kSteps], qs = 0;
-    const int64_t rk = clamp_hi(rs + 8 * li, a.red - 8);
 #pragma unroll
     for (int t = 0; t < kSteps; ++t) {
+      // 4-bit factors: row 4 t + g of a fragment, whole; fp16 ones: row lane % 16, step t's positions
+      const int64_t rk = clamp_hi(rs + (QA ? 8 * li : 32 * t + 8 * g), a.red - 8);
 #pragma unroll
       for (int f = 0; f < FM; ++f)
-        aq[t][f] = *reinterpret_cast<const u32x4_t*>(a.act + clamp_hi(16 * f + 4 * t + g, a.M - 1) * a.red + rk);
-      if (!QA) bq[t] = *reinterpret_cast<const u32x4_t*>(a.ad_q + clamp_hi(jb * 16 + 4 * t + g, a.r - 1) * a.red + rk);
+        aq[t][f] = *reinterpret_cast<const u32x4_t*>(a.act + clamp_hi(16 * f + (QA ? 4 * t + g : li), a.M - 1) * a.red + rk);
+      if (!QA) bq[t] = *reinterpret_cast<const u32x4_t*>(a.ad_q + jl * a.red + rk);
     }
     // 16 rows of 64 bytes: lane / 4 the row, lane % 4 the 16-byte piece
     if (QA)
       bq[0] = __builtin_bit_cast(u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(
           rq4, (uint32_t)(clamp_hi(jb * 16 + (lane >> 2), a.r - 1) * (a.red / 2) + clamp_hi(rs, a.red - 128) / 2) + 16u * (lane & 3), 0, 0));
     if (QA) qs = a.q4s[jl * ngk + clamp_hi(rs / 128, ngk - 1)];
-#pragma unroll
-    for (int f = 0; f < FM; ++f) turn(&aq[0][f], FM, mine + 256 * f);
     if (QA) {
+#pragma unroll
+      for (int f = 0; f < FM; ++f) turn(&aq[0][f], FM, mine + 256 * f);
       mine[lane] = bq[0];
 #pragma unroll
       for (int t = 0; t < kSteps; ++t) qw[t] = reinterpret_cast<const uint32_t*>(mine)[16 * li + 4 * t + g];
-    } else {
-      turn(bq, 1, mine);
     }
     // this round's activations of row m = 16 f + lane % 16, scaled per row (see act_exponent): the
     // four lane groups of a row exchange their maxima; the round's product is unscaled in fp32
@@ -426,7 +426,7 @@ SLIM_DEV void decode_adapter_unit(const LayerArgs& a, int64_t v, f4_t* red_lds) 
   else rounds(std::false_type{});
   // the unit's sum: waves 1..3 hand theirs (and their maxima) to wave 0 through LDS
   __shared__ uint32_t mx_lds[3][FM][64];
-  __syncthreads();
+  if (QA) __syncthreads();
   if (wave > 0)
 #pragma unroll
     for (int f = 0; f < FM; ++f) {
