@@ -71,6 +71,15 @@ def test_linear_qa_small_m_ranks(m, r):
     _case(1024, 2048, r, m, name="qsmall")
 
 
+# The codes' loads of whole pieces: reductions shorter than a unit's, ranks that are not whole 128-groups, ranks
+# of more than one pass, and one, two and four finish waves (more than 16384, 4096 rows), for one and two fragments
+@pytest.mark.parametrize("n,k,r,m", [(48, 128, 32, 1), (528, 256, 96, 8), (4096, 640, 224, 5), (5120, 1152, 480, 16),
+                                     (4112, 384, 1056, 9), (16400, 256, 160, 3), (2064, 640, 288, 17),
+                                     (16400, 128, 32, 32)])
+def test_linear_qa_code_pieces(n, k, r, m):
+    _case(n, k, r, m, name="qpieces")
+
+
 @pytest.mark.parametrize("m,r", [(200, 64), (33, 96), (300, 32)])
 def test_linear_qa_large_m(m, r):
     _case(1024, 1024, r, m, name="qlarge")
