@@ -574,17 +574,18 @@ HybridPlan hybrid_plan(int64_t M, int64_t N, int64_t K) {
   int64_t most = p.tiles < 256 ? (512 + p.tiles - 1) / p.tiles : 1;     // no more than two rounds of blocks
   if (most > chunks) most = chunks;
   double best = 0;
-  for (int64_t want = 1; want <= most; ++want) {
-    const int64_t cps = (chunks + want - 1) / want, s = (chunks + cps - 1) / cps;
-    if (s < want) continue;
-    const double full = 4.5 + 2.0 * cps, last = 4.5 + 2.0 * (chunks - (s - 1) * cps);
+  const uint32_t nch = (uint32_t)chunks;               // at most 256
+  for (uint32_t s = 1; s <= (uint32_t)most; ++s) {
+    const uint32_t cps = (nch + s - 1) / s;
+    if (cps * (s - 1) >= nch) continue;                 // fewer splits of as many chunks
+    const double full = 4.5 + 2.0 * cps, last = 4.5 + 2.0 * (nch - (s - 1) * cps);
     const int64_t nfull = p.tiles * (s - 1), busy = nfull % 256, idle = 256 - busy;
     // whole rounds, then the busy blocks' end or the last split's, in as many rounds as the idle CUs need
     double t = full * (double)(nfull / 256);
     const double ends = last * (double)((p.tiles + idle - 1) / idle), both = (busy ? full : 0) + last * (double)((p.tiles + 255) / 256);
     t += busy && ends < full ? full : (ends < both ? ends : both);
-    if (s > 1) t += 3.0 + (double)s * M * N * 8 / 7e6;
-    if (want == 1 || t < best) {
+    if (s > 1) t += 3.0 + (double)s * (double)M * (double)N * (8 / 7e6);
+    if (s == 1 || t < best) {
       best = t;
       p.splits = s;
       p.chunks_per_split = cps;
