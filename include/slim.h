@@ -73,7 +73,8 @@
  *     M > 32 it is formed from the row-scaled activations and stored in fp16, so its entries
  *     must stay below 65504 after that scaling: |T[m, j]| < 2^11 max_k |X[m, k]| (true when
  *     sum_k |L[k, j]| < 2^11).
- * Deterministic: identical inputs give identical bits.
+ * Deterministic: identical inputs (and at M > 32 a workspace that holds the same kernels, see
+ * slim_linear_workspace) give identical bits.
  */
 #ifndef SLIM_H
 #define SLIM_H
@@ -94,7 +95,7 @@ typedef enum {
   SLIM_EDTYPE = 3,        /* unsupported dtype code */
   SLIM_EALIGN = 4,        /* a device array is not 16-byte aligned */
   SLIM_ENONFINITE = 5,    /* W holds a NaN or an infinity */
-  SLIM_EWORKSPACE = 6,    /* workspace missing or smaller than the query returned */
+  SLIM_EWORKSPACE = 6,    /* workspace missing or too small for the call's kernels */
   SLIM_EDEVICE = 7,       /* a HIP runtime call or a kernel launch failed */
   SLIM_EUNSUPPORTED = 8,  /* valid but not supported by this library (e.g. no gfx950 device) */
   SLIM_ERANGE = 9         /* a group scale the packed format or the backward cannot represent */
@@ -206,13 +207,17 @@ int slim_pack_adapter_q(const uint16_t* L, const uint16_t* R, int64_t K, int64_t
                         uint16_t* Ls, uint8_t* Rq, uint16_t* Rs, void* stream);
 
 /*
- * slim_linear_workspace - bytes of device workspace slim_linear needs for these sizes
- * (written to *bytes, host pointer). Depends only on the sizes. Pure host function.
+ * slim_linear_workspace - bytes of device workspace with which slim_linear runs its fastest kernels for
+ * these sizes (written to *bytes, host pointer). Depends only on the sizes. Pure host function.
+ * The figure does not always grow with M: a workspace for calls of several M should have the largest of
+ * their figures. At M > 32 a smaller one may still hold the kernels that take the least (512-row tiles);
+ * the call then runs those, slower for some hundred rows and with its sums in another order, and returns
+ * SLIM_EWORKSPACE only if they do not fit either.
  */
 int slim_linear_workspace(int64_t M, int64_t N, int64_t K, int64_t r, size_t* bytes);
 
 /*
- * slim_bwd_dx_workspace - bytes of device workspace slim_linear_bwd_dx needs. Pure host function.
+ * slim_bwd_dx_workspace - the same for slim_linear_bwd_dx. Pure host function.
  */
 int slim_bwd_dx_workspace(int64_t M, int64_t N, int64_t K, int64_t r, size_t* bytes);
 
@@ -234,8 +239,8 @@ int slim_workspace_init(void* ws, size_t ws_bytes, void* stream);
  *           in 32 x 16 tiles (a plain row-major R^T gives wrong results); both NULL when
  *           r == 0. r % 16 == 0.
  *   Y       out, fp32 [M, N]. Must not alias any input.
- *   ws      device workspace of at least slim_linear_workspace(M, N, K, r) bytes, zeroed once
- *           with slim_workspace_init before its first use. Two calls that overlap in time must
+ *   ws      device workspace of slim_linear_workspace(M, N, K, r) bytes or more (see there for less), zeroed
+ *           once with slim_workspace_init before its first use. Two calls that overlap in time must
  *           not share a workspace.
  * Sizes past the kernels' 32-bit offsets return SLIM_EUNSUPPORTED: for M > 32, K above 2^23, or
  * ceil(M/32)*32*r or ceil(N/32)*32*r of 2^30 or more.
@@ -253,7 +258,8 @@ int slim_linear(const void* X, int xdtype, int64_t M, int64_t N, int64_t K, cons
  * results and speedup tables).
  *
  *   Arguments as slim_linear, with Lq, Ls, Rq, Rs in place of Lt, Rt; r >= 32, r % 32 == 0.
- *   ws      at least slim_linear_qa_workspace(M, N, K, r) bytes, zeroed once with slim_workspace_init.
+ *   ws      slim_linear_qa_workspace(M, N, K, r) bytes (for less see slim_linear_workspace), zeroed once with
+ *           slim_workspace_init.
  * At M <= 32 the kernels dequantize the factors in registers as they stream them; at M > 32 the
  * first launch expands them to fp16 in the workspace. The dequantized factor values are
  * (u - 8) * s16 rounded to fp16 (as for the weights); otherwise precision as slim_linear.
@@ -274,7 +280,7 @@ int slim_linear_qa(const void* X, int xdtype, int64_t M, int64_t N, int64_t K, c
  *   codesT, metaT, scalesT   backward pack (slim_pack_bwd).
  *   L, R    fp16 [K, r] and [r, N]; both NULL when r == 0. r % 16 == 0.
  *   dX      out, fp32 [M, K].
- *   ws      workspace of at least slim_bwd_dx_workspace(M, N, K, r) bytes, zeroed once.
+ *   ws      workspace of slim_bwd_dx_workspace(M, N, K, r) bytes (for less see slim_linear_workspace), zeroed once.
  * Sizes past the kernels' 32-bit offsets return SLIM_EUNSUPPORTED: for M > 32, N above 2^23, or
  * ceil(M/32)*32*r or ceil(K/32)*32*r of 2^30 or more.
  * Operand precision: the weight codes enter the matrix cores as exact small integers; the fp16
@@ -295,7 +301,7 @@ int slim_linear_bwd_dx(const void* dY, int dydtype, int64_t M, int64_t N, int64_
  * library holds per device from the first call on that device until the process ends; its first
  * call on a device also enqueues a small kernel that clears the array's counter region. The call
  * allocates nothing (no hipMalloc, hipFree or allocating library routine) and records no timing
- * events. Sizes whose slim_linear_workspace exceeds SLIM_NOALLOC_SCRATCH_BYTES return
+ * events. Sizes whose kernels need more than SLIM_NOALLOC_SCRATCH_BYTES return
  * SLIM_EWORKSPACE before touching any device; that covers every M <= 32 layer of the shapes here
  * and the 11008 x 4096 layer at M = 2048, but not, for example, a 5120 x 5120 layer at M = 4096.
  * All calls on one device share its array, so two calls that overlap in time on one device

@@ -116,8 +116,9 @@ bool mid_plan(bool bwd, int64_t M, int64_t rows, int64_t red, int64_t r, SlimPla
   return true;
 }
 
-// `fewest`: the plan with the least workspace (512-row tiles and the 128 x 128 adapter kernel at M > 32).
-int make_plan(bool bwd, int64_t M, int64_t N, int64_t K, int64_t r, bool fewest, SlimPlan* p) {
+// One plan. `rows512` (M > 32): 512-row tiles and the kernels of k_adapter_gemm; otherwise the middle path or its
+// first-product units where they are the faster ones.
+int plan_kernels(bool bwd, int64_t M, int64_t N, int64_t K, int64_t r, bool rows512, SlimPlan* p) {
   if (M < 1 || N < 16 || K < 128 || M >= kMaxDim || N >= kMaxDim || K >= kMaxDim) return SLIM_ESHAPE;
   if (N % 16 || K % 128 || r < 0 || r % 16 || r >= kMaxDim) return SLIM_ESHAPE;
   if (bwd && N % 128) return SLIM_ESHAPE;
@@ -169,7 +170,7 @@ int make_plan(bool bwd, int64_t M, int64_t N, int64_t K, int64_t r, bool fewest,
     if (red > kMaxLargeRed || cdiv(M, 32) * 32 * r >= kMaxTiledElems || cdiv(rows, 32) * 32 * r >= kMaxTiledElems)
       return SLIM_EUNSUPPORTED;
     q.decode = false;
-    if (!fewest && mid_plan(bwd, M, rows, red, r, &q)) {
+    if (!rows512 && mid_plan(bwd, M, rows, red, r, &q)) {
       if (q.sp_split > 1 || r > 0)
         ypart_bytes = (size_t)q.sp_split * (size_t)(q.sp_row_tiles * q.sp_rows_tile) * (size_t)(q.sp_col_tiles * q.sp_cols_tile) * 4;
       if (q.ad_split > 1) {
@@ -203,7 +204,7 @@ int make_plan(bool bwd, int64_t M, int64_t N, int64_t K, int64_t r, bool fewest,
         q.ad_split = (int)cdiv(red, slice);
         q.ad_slice = slice;
         if (q.ad_split > 1) tpart_bytes = (size_t)q.ad_split * (size_t)cdiv(M, 32) * 32 * (size_t)r * 4;
-      } else if (r > 0 && !fewest && cdiv(M, 128) * cdiv(r, 128) <= 64) {
+      } else if (r > 0 && !rows512 && cdiv(M, 128) * cdiv(r, 128) <= 64) {
         // few tiles of T: the middle path's first-product units, which sum their slices in the launch (7B
         // prefill 11008 x 4096, M 2048, r 384 (48 tiles): 20.0 against 19.4 us and a 5.3 us launch that sums;
         // 28672 x 8192, M 512 (16): 20.8 against 17.6 + 6.0). With more tiles two 128 x 128 blocks per CU are
@@ -260,16 +261,28 @@ int make_plan(bool bwd, int64_t M, int64_t N, int64_t K, int64_t r, bool fewest,
   q.off_pb = off;
   if (!q.decode && bwd) off = round256(off + (size_t)cdiv(rows, 32) * 32 * (size_t)r * 2);
   q.total = off;
-  // sizes that fit the no-allocation entry point's scratch on the 512-row tiles keep fitting
-  if ((q.mid || q.ad_tn) && q.total > (size_t)SLIM_NOALLOC_SCRATCH_BYTES) return make_plan(bwd, M, N, K, r, true, p);
+  q.query = off;
   *p = q;
   return SLIM_OK;
 }
 
 }  // namespace
 
-int slim_make_plan(bool bwd, int64_t M, int64_t N, int64_t K, int64_t r, SlimPlan* p) {
-  return make_plan(bwd, M, N, K, r, false, p);
+// The faster plan where the workspace holds it, the 512-row one where it does not: the faster plan's size falls
+// and rises with M (4096 x 4096, r 384: 46.0 MB at M 1280, 29.5 MB at M 2048), so a workspace made for a program's
+// most rows may be short for it with fewer. The query is the larger of the two sizes, so that it also covers every
+// smaller M that the 512-row plans' sizes cover.
+int slim_make_plan(bool bwd, int64_t M, int64_t N, int64_t K, int64_t r, size_t ws_bytes, SlimPlan* p) {
+  int st = plan_kernels(bwd, M, N, K, r, true, p);
+  if (st != SLIM_OK || p->decode) return st;
+  SlimPlan q;
+  st = plan_kernels(bwd, M, N, K, r, false, &q);
+  if (st != SLIM_OK) return st;
+  // sizes that fit the no-allocation entry point's scratch on the 512-row tiles keep fitting
+  if ((q.mid || q.ad_tn) && q.total > (size_t)SLIM_NOALLOC_SCRATCH_BYTES) return SLIM_OK;
+  q.query = p->query = std::max(p->total, q.total);
+  if (q.total <= ws_bytes) *p = q;
+  return SLIM_OK;
 }
 
 int slim_check_linear(bool bwd, const void* X, int xdtype, int64_t M, int64_t N, int64_t K, const void* codes,
@@ -279,7 +292,7 @@ int slim_check_linear(bool bwd, const void* X, int xdtype, int64_t M, int64_t N,
   if (r < 0) return SLIM_EINVAL;
   if (r == 0 ? (L != nullptr || R != nullptr) : (!L || !R)) return SLIM_EINVAL;
   if (xdtype != SLIM_F16 && xdtype != SLIM_BF16) return SLIM_EDTYPE;
-  int st = slim_make_plan(bwd, M, N, K, r, plan);
+  int st = slim_make_plan(bwd, M, N, K, r, ws_bytes, plan);
   if (st != SLIM_OK) return st;
   if (!slim_aligned16(X) || !slim_aligned16(codes) || !slim_aligned16(meta) || !slim_aligned16(scales) ||
       !slim_aligned16(Y) || (L && !slim_aligned16(L)) || (R && !slim_aligned16(R)))
@@ -293,31 +306,33 @@ int slim_check_linear(bool bwd, const void* X, int xdtype, int64_t M, int64_t N,
 extern "C" int slim_linear_workspace(int64_t M, int64_t N, int64_t K, int64_t r, size_t* bytes) {
   if (!bytes) return SLIM_EINVAL;
   SlimPlan p;
-  int st = slim_make_plan(false, M, N, K, r, &p);
-  if (st == SLIM_OK) *bytes = p.total;
+  int st = slim_make_plan(false, M, N, K, r, SIZE_MAX, &p);
+  if (st == SLIM_OK) *bytes = p.query;
   return st;
 }
 
 extern "C" int slim_bwd_dx_workspace(int64_t M, int64_t N, int64_t K, int64_t r, size_t* bytes) {
   if (!bytes) return SLIM_EINVAL;
   SlimPlan p;
-  int st = slim_make_plan(true, M, N, K, r, &p);
-  if (st == SLIM_OK) *bytes = p.total;
+  int st = slim_make_plan(true, M, N, K, r, SIZE_MAX, &p);
+  if (st == SLIM_OK) *bytes = p.query;
   return st;
 }
 
-int slim_make_plan_qa(int64_t M, int64_t N, int64_t K, int64_t r, SlimPlan* p) {
+int slim_make_plan_qa(int64_t M, int64_t N, int64_t K, int64_t r, size_t ws_bytes, SlimPlan* p) {
   if (r < 32 || r % 32) return SLIM_ESHAPE;   // 4-bit factor rows are whole 16-byte runs
-  int st = slim_make_plan(false, M, N, K, r, p);
-  if (st != SLIM_OK) return st;
-  if (!p->decode) {
-    size_t off = p->total;
-    p->off_q16 = off;
-    off = round256(off + (size_t)r * (size_t)K * 2);
-    p->off_p16 = off;
-    off = round256(off + (size_t)cdiv(N, 32) * 32 * (size_t)r * 2);
-    p->total = off;
+  // the expansions follow the layer's own workspace (whose end is a multiple of 256)
+  size_t q16 = 0, p16 = 0;
+  if (M > 32 && N > 0 && K > 0 && N < kMaxDim && K < kMaxDim && r < kMaxDim) {
+    q16 = round256((size_t)r * (size_t)K * 2);
+    p16 = round256((size_t)cdiv(N, 32) * 32 * (size_t)r * 2);
   }
+  int st = slim_make_plan(false, M, N, K, r, ws_bytes > q16 + p16 ? ws_bytes - q16 - p16 : 0, p);
+  if (st != SLIM_OK) return st;
+  p->off_q16 = p->total;
+  p->off_p16 = p->total + q16;
+  p->total += q16 + p16;
+  p->query += q16 + p16;
   return SLIM_OK;
 }
 
@@ -326,7 +341,7 @@ int slim_check_linear_qa(const void* X, int xdtype, int64_t M, int64_t N, int64_
                          const void* Rs, int64_t r, const void* Y, const void* ws, size_t ws_bytes, SlimPlan* plan) {
   if (!X || !codes || !meta || !scales || !Y || !Lq || !Ls || !Rq || !Rs) return SLIM_EINVAL;
   if (xdtype != SLIM_F16 && xdtype != SLIM_BF16) return SLIM_EDTYPE;
-  int st = slim_make_plan_qa(M, N, K, r, plan);
+  int st = slim_make_plan_qa(M, N, K, r, ws_bytes, plan);
   if (st != SLIM_OK) return st;
   if (!slim_aligned16(X) || !slim_aligned16(codes) || !slim_aligned16(meta) || !slim_aligned16(scales) ||
       !slim_aligned16(Y) || !slim_aligned16(Lq) || !slim_aligned16(Ls) || !slim_aligned16(Rq) || !slim_aligned16(Rs))
@@ -340,7 +355,7 @@ int slim_check_linear_qa(const void* X, int xdtype, int64_t M, int64_t N, int64_
 extern "C" int slim_linear_qa_workspace(int64_t M, int64_t N, int64_t K, int64_t r, size_t* bytes) {
   if (!bytes) return SLIM_EINVAL;
   SlimPlan p;
-  int st = slim_make_plan_qa(M, N, K, r, &p);
-  if (st == SLIM_OK) *bytes = p.total;
+  int st = slim_make_plan_qa(M, N, K, r, SIZE_MAX, &p);
+  if (st == SLIM_OK) *bytes = p.query;
   return st;
 }

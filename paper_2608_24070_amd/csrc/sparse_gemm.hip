@@ -1560,7 +1560,7 @@ extern "C" int slim_linear_noalloc(const void* X, int xdtype, int64_t M, int64_t
                                    const uint16_t* Rt, int64_t r, float* Y, void* stream) {
   // the size checks come first, so a call the scratch cannot hold touches no device
   SlimPlan p;
-  int st = slim_make_plan(false, M, N, K, r, &p);
+  int st = slim_make_plan(false, M, N, K, r, SLIM_NOALLOC_SCRATCH_BYTES, &p);
   if (st != SLIM_OK) return st;
   if (p.total > (size_t)SLIM_NOALLOC_SCRATCH_BYTES) return SLIM_EWORKSPACE;
   hipStream_t s = (hipStream_t)stream;

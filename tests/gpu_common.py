@@ -80,6 +80,19 @@ def layer_inputs(n, k, r, m, seed=0, xdtype="bf16", outliers=False, name="layer"
     return W, X, L, R, dx, ad
 
 
+def kernels_of(call):
+    """Names of the library's kernels that `call` launches."""
+    slim.slim_timing_reset()
+    slim.slim_timing_enable(True)
+    try:
+        call()
+    finally:
+        slim.slim_timing_enable(False)
+    names = set(slim.slim_timing_read())
+    slim.slim_timing_reset()
+    return names
+
+
 def assert_close(Y, Yref, what=""):
     ok, rf, ma = O.within_tolerance(Y, Yref, TOL_REL_FRO, TOL_MAX_ABS)
     assert np.all(np.isfinite(Y)), f"{what}: non-finite output"

@@ -167,6 +167,56 @@ def _rows512_workspace(M, N, K, r):
     return up(up(off + M * K * 2) + M * 4)
 
 
+def _rows512_bwd(M, N, K, r):
+    # the same with rows K and reduction N, and the re-laid second factor
+    return _rows512_workspace(M, K, N, r) + (-(-K // 32) * 32 * r * 2 + 255) // 256 * 256
+
+
+def _rows512_qa(M, N, K, r):
+    # the same and the fp16 expansions of the 4-bit factors
+    return _rows512_workspace(M, N, K, r) + r * K * 2 + -(-N // 32) * 32 * r * 2
+
+
+def _ws_status(kind, M, N, K, r, ws_bytes):
+    """Status of a call with a workspace of ws_bytes at a misaligned address: SLIM_EALIGN where the size is
+    accepted (the address is looked at after it), so that nothing is ever launched."""
+    f = A if r else None
+    if kind == "fwd":
+        return slim.slim_linear(A, 1, M, N, K, A, A, A, f, f, r, A, MIS, ws_bytes, None)
+    if kind == "qa":
+        return slim.slim_linear_qa(A, 1, M, N, K, A, A, A, A, A, A, A, r, A, MIS, ws_bytes, None)
+    return slim.slim_linear_bwd_dx(A, 1, M, N, K, A, A, A, f, f, r, A, MIS, ws_bytes, None)
+
+
+_ROWS512 = {"fwd": _rows512_workspace, "dx": _rows512_bwd, "qa": _rows512_qa}
+_QUERY = {"fwd": slim.slim_linear_workspace, "dx": slim.slim_bwd_dx_workspace, "qa": slim.slim_linear_qa_workspace}
+
+
+@pytest.mark.parametrize("kind", ["fwd", "dx", "qa"])
+def test_workspaces_of_the_512_row_tiles_are_accepted(kind):
+    # the faster kernels may take more than the 512-row tiles; a workspace that holds the latter is never refused
+    import random
+    rng = random.Random(6)
+    for _ in range(5000):
+        n, k = 128 * rng.randint(1, 224), 128 * rng.randint(1, 224)
+        m, r = rng.randint(33, 700) if rng.random() < 0.7 else rng.randint(33, 8192), 32 * rng.randint(kind == "qa", 32)
+        base, need = _ROWS512[kind](m, n, k, r), _QUERY[kind](m, n, k, r)
+        assert need >= base, (m, n, k, r)
+        assert _ws_status(kind, m, n, k, r, base) == slim.SLIM_EALIGN, (m, n, k, r)
+        assert _ws_status(kind, m, n, k, r, need) == slim.SLIM_EALIGN, (m, n, k, r)
+        least = 4096 * 4 + 2 * m * r + 2 * m * (n if kind == "dx" else k)    # counters, T and the activations
+        assert _ws_status(kind, m, n, k, r, least - 1) == slim.SLIM_EWORKSPACE, (m, n, k, r)
+
+
+@pytest.mark.parametrize("kind,top,n,k,r", [("fwd", 2048, 4096, 4096, 384), ("fwd", 512, 4096, 4096, 0),
+                                            ("dx", 512, 5120, 13824, 512), ("qa", 2048, 4096, 4096, 384)])
+def test_a_workspace_for_the_most_rows_serves_fewer(kind, top, n, k, r):
+    ws = _QUERY[kind](top, n, k, r)
+    assert max(_QUERY[kind](m, n, k, r) for m in range(33, top)) > ws     # sizes whose faster kernels take more
+    for m in range(33, top):
+        assert _ws_status(kind, m, n, k, r, ws) == slim.SLIM_EALIGN, m
+
+
 def test_sizes_that_fit_the_noalloc_scratch_on_512_row_tiles_still_fit():
     # the middle path's partials and slices may take more workspace, but never push a size out of the scratch
     import random

@@ -7,7 +7,7 @@ import torch
 
 from oracle import slim_oracle as O
 from paper_2608_24070_amd import slim, synth
-from tests.gpu_common import assert_close, dev, dev_bits, host, layer_inputs
+from tests.gpu_common import assert_close, dev, dev_bits, host, kernels_of, layer_inputs
 
 pytestmark = pytest.mark.gpu
 
@@ -76,6 +76,60 @@ def test_backward_edges(n, k, r, m, xdtype):
                                    synth.stream(2, "m").choice(m, size=min(m, 40), replace=False)]))
     ref = O.bwd_dx(dY[ms], O.pack_bwd(O.pack(W), n, k), L[:, :r] if r else None, R[:r] if r else None, n, k)
     assert_close(host(dX)[ms], ref, f"mid bwd n={n} k={k} r={r} m={m}")
+
+
+def _least(call):
+    """The smallest workspace (in steps of 256 bytes) that `call(nbytes)` is not refused with."""
+    lo, hi = 0, 1 << 18
+    while lo < hi:
+        mid = (lo + hi) // 2
+        lo, hi = (mid + 1, hi) if call(256 * mid) == slim.SLIM_EWORKSPACE else (lo, mid)
+    return 256 * lo
+
+
+A = 1 << 20      # an address that is only looked at, never used: the workspace beside it is misaligned
+
+
+@pytest.mark.parametrize("n,k,r,m", [(528, 2048, 272, 128), (80, 640, 32, 100), (2048, 4096, 64, 333)])
+@pytest.mark.parametrize("kind", ["fwd", "qa", "dx"])
+def test_short_workspace_runs_the_512_row_tiles(kind, n, k, r, m):
+    # a workspace too small for the middle path: the least one that is accepted, and guard bytes behind it
+    if kind == "dx":
+        n = (n + 127) // 128 * 128
+    if kind == "qa":
+        r = (r + 31) // 32 * 32
+    print(f"short ws {kind} n={n} k={k} r={r} m={m}", flush=True)
+    W, X, L, R, dx, ad = layer_inputs(n, k, r, m, name="short")
+    p = slim.pack(dev(W))
+    if kind == "fwd":
+        full = slim.slim_linear_workspace(m, n, k, r)
+        least = _least(lambda b: slim.slim_linear(A, 1, m, n, k, A, A, A, A, A, r, A, A + 4, b, None))
+        run = lambda ws: slim.linear(dx, p, ad, ws=ws)
+        ref = O.linear(X, O.pack(W), L, R, n, k)
+    elif kind == "qa":
+        full = slim.slim_linear_qa_workspace(m, n, k, r)
+        least = _least(lambda b: slim.slim_linear_qa(A, 1, m, n, k, A, A, A, A, A, A, A, r, A, A + 4, b, None))
+        q = slim.pack_adapter_q(ad["L"], ad["R"])
+        run = lambda ws: slim.linear_qa(dx, p, q, ws=ws)
+        ref = O.linear_qa(X, O.pack(W), O.pack_adapter_q(L, R), n, k, r)
+    else:
+        full = slim.slim_bwd_dx_workspace(m, n, k, r)
+        least = _least(lambda b: slim.slim_linear_bwd_dx(A, 1, m, n, k, A, A, A, A, A, r, A, A + 4, b, None))
+        yb, dY = synth.activations(m, n, seed=2, name="short/dY")
+        dy, pb = dev_bits(yb, torch.bfloat16), slim.pack_bwd(p)
+        run = lambda ws: slim.bwd_dx(dy, pb, ad["L"], ad["R"], ws=ws)
+        ref = O.bwd_dx(dY, O.pack_bwd(O.pack(W), n, k), L, R, n, k)
+    assert least < full
+    buf = _ws(least + 4096)
+    buf[least:] = 0x5A
+    ws = buf[:least]
+    names = kernels_of(lambda: run(ws))
+    assert any(x.startswith("tile_") for x in names) and not any(x.startswith("mid_") for x in names), names
+    assert any(x.startswith("mid_") for x in kernels_of(lambda: run(_ws(full))))
+    Y = run(ws)
+    assert_close(host(Y), ref, f"short ws {kind}")
+    assert torch.equal(Y, run(ws).clone())
+    assert _counters_zero(buf) and bool((buf[least:] == 0x5A).all())
 
 
 @pytest.mark.parametrize("n,k,r,m", [(11008, 1024, 80, 1000), (4096, 1024, 400, 2048)])
