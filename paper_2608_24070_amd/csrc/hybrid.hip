@@ -377,8 +377,8 @@ k_hybrid_gemm(HybridArgs g) {
 }
 
 // ------------------------------------------------------------------------------------- few rows
-// M <= 16 MF: bound by the reading of the weights. A block takes 16 RF rows of one tile row with W waves
-// that share K chunk by chunk (wave w takes chunks w, w + W, ...), and adds their sums through LDS in wave order:
+// Bound by the reading of the weights. A block takes 16 RF rows of one tile row and 16 MF rows of X with W waves
+// that share K chunk by chunk (wave w takes chunks w, w + W, ...), and adds their sums through LDS in a fixed order:
 // no partials in memory and no second launch. A wave loads its weights and its activations (from the L2) itself,
 // two chunks in flight, X and dense weights as whole rows of a chunk (256 bytes); it turns them through its own
 // LDS, without a barrier, into the MFMA's operand layout, which loaded directly is 64-byte pieces of 16 rows
@@ -395,11 +395,11 @@ k_hybrid_few(HybridArgs g) {
   f4_t* part = reinterpret_cast<f4_t*>(&stage[0][0][0]);
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int li = lane & 15, lg = lane >> 4;
-  const int64_t n0 = (int64_t)blockIdx.x * 16 * RF;
+  const int64_t n0 = (int64_t)blockIdx.x * 16 * RF, m0 = (int64_t)blockIdx.y * 16 * MF;
   const int chunks = (int)(g.K / kHT);
   const uint64_t* info = g.info + (n0 / kHT) * chunks;
   const int rt = (int)(n0 % kHT), r0 = rt + li;
-  const rsrc_t rw = make_rsrc(g.payload, g.payload_bytes), rx = make_rsrc(g.X, g.M * g.K * 2);
+  const rsrc_t rw = make_rsrc(g.payload, g.payload_bytes), rx = make_rsrc(g.X + m0 * g.K, (g.M - m0) * g.K * 2);
   // whole rows of 256 bytes: load i of a fragment takes row 4 i + lg, 16-byte slot li (X rows past M read as
   // zero); the wave's LDS keeps slot s of row r at s ^ r, so neither the writes nor the reads below, lane (li, lg)
   // taking slot 4 t + lg of row li, conflict
@@ -448,17 +448,24 @@ k_hybrid_few(HybridArgs g) {
 #pragma unroll
       for (int t = 0; t < 4; ++t) S.x[m][t] = load16(rx, xo[m][t], (uint32_t)c * 256u);
   };
-  // of the wave's even and odd chunks, where the registers allow it: shorter chains of roundings
-  constexpr int kAcc = W > 4 && MF < 4 ? 2 : 1;
-  f4_t acc[kAcc][RF][MF];
+  // the sum of two chunks, and that of the pairs before them: one sum of all chunks would be a chain of up to 28
+  // chunks' roundings (32 x 11008 x 14336 is 3.3e-7 from 64 bits with it, 2.1e-7 on k_hybrid_gemm's splits)
+  f4_t acc[RF][MF], tot[RF][MF];
 #pragma unroll
-  for (int a = 0; a < kAcc; ++a)
+  for (int f = 0; f < RF; ++f)
+#pragma unroll
+    for (int m = 0; m < MF; ++m) acc[f][m] = tot[f][m] = f4_t{0.f, 0.f, 0.f, 0.f};
+  auto carry = [&]() {
 #pragma unroll
     for (int f = 0; f < RF; ++f)
 #pragma unroll
-      for (int m = 0; m < MF; ++m) acc[a][f][m] = f4_t{0.f, 0.f, 0.f, 0.f};
+      for (int m = 0; m < MF; ++m) {
+        tot[f][m] += acc[f][m];
+        acc[f][m] = f4_t{0.f, 0.f, 0.f, 0.f};
+      }
+  };
   auto h8 = [](u32x4_t v) { return __builtin_bit_cast(h8_t, v); };
-  auto compute = [&](Set& S, f4_t (&acc)[RF][MF]) {
+  auto compute = [&](Set& S) {
     auto turn = [&](u32x4_t (&v)[4], u32x4_t* buf) {
 #pragma unroll
       for (int i = 0; i < 4; ++i) buf[wr[i]] = v[i];
@@ -493,10 +500,11 @@ k_hybrid_few(HybridArgs g) {
     load(A, c);
     while (true) {
       if (c + W < chunks) load(B, c + W);
-      compute(A, acc[0]);
+      compute(A);
       if (c + W >= chunks) break;
       if (c + 2 * W < chunks) load(A, c + 2 * W);
-      compute(B, acc[kAcc - 1]);
+      compute(B);
+      carry();
       if (c + 2 * W >= chunks) break;
       c += 2 * W;
     }
@@ -505,15 +513,19 @@ k_hybrid_few(HybridArgs g) {
 #pragma unroll
   for (int f = 0; f < RF; ++f)
 #pragma unroll
-    for (int m = 0; m < MF; ++m) part[(wave * RF * MF + f * MF + m) * 64 + lane] = kAcc > 1 ? acc[0][f][m] + acc[kAcc - 1][f][m] : acc[0][f][m];
+    for (int m = 0; m < MF; ++m) part[(wave * RF * MF + f * MF + m) * 64 + lane] = tot[f][m] + acc[f][m];
   __syncthreads();
   // D[i][j] of a 16 x 16 fragment: lane j + 16 (i / 4), element i % 4
   for (int t = tid; t < 64 * RF * MF; t += 64 * W) {
     const int fr = t >> 6;
-    f4_t o = part[fr * 64 + lane];
+    f4_t q[4];
 #pragma unroll
-    for (int w = 1; w < W; ++w) o += part[(w * RF * MF + fr) * 64 + lane];
-    const int64_t m = 16 * (fr % MF) + li, nn = n0 + 16 * (fr / MF) + 4 * lg;
+    for (int w = 0; w < W; ++w) {
+      const f4_t v = part[(w * RF * MF + fr) * 64 + lane];
+      q[w % 4] = w < 4 ? v : q[w % 4] + v;
+    }
+    const f4_t o = (q[0] + q[1]) + (q[2] + q[3]);
+    const int64_t m = m0 + 16 * (fr % MF) + li, nn = n0 + 16 * (fr / MF) + 4 * lg;
     if (m < g.M) *reinterpret_cast<f4_t*>(g.out + m * g.N + nn) = o;
   }
 }
@@ -544,8 +556,8 @@ k_hybrid_reduce(const float* __restrict__ part, int splits, int64_t count4, floa
 //   M <= 16: always (16 x 11008 x 4096: 13.7 us against 20.8, 16 x 1024 x 1024 3.0 against 7.8, 14336 x 14336 59
 //     against 72; 512 x 14336 level at 12; the sums' chains are no longer than in the GEMM's splits)
 //   M <= 32: unless few row blocks each have a long chain (32 x 512 x 14336: 18.7 against 13.9; 4096 x 11008
-//     17.5 against 22.4, 14336 x 14336 72 against 74)
-//   M <= 64: up to 4096 x 4096 (64 rows: 12.7 against 16.7; 11008 x 4096: 30.4 against 27.8)
+//     17.5 against 22.4, 11008 x 14336 52 against 59, 14336 x 14336 74 against 80)
+//   M <= 64: in two halves, up to 4096 x 4096 (64 rows: 10.1 against 17.4, 2048 x 4096 7.6 against 12.4)
 bool hybrid_few(int64_t M, int64_t N, int64_t K) {
   if (M <= 16) return true;
   if (M <= 32) return N > 2048 || K <= 8192;
@@ -681,23 +693,22 @@ extern "C" int slim_linear_hybrid(const void* X, int64_t M, int64_t N, int64_t K
   if (p.few) {
     const HybridArgs a{static_cast<const uint16_t*>(X), tile_info, payload, Y, M, N, K, (int64_t)payload_bytes, 0};
     SlimKernelTimer timer("hybrid_few", s);
+    const int64_t cols = (M + 31) / 32;
     auto go = [&](auto kernel, int rows, int waves) {
-      SLIM_LAUNCH(timer, kernel, dim3((unsigned)(N / rows)), dim3((unsigned)(64 * waves)), s, a);
+      SLIM_LAUNCH(timer, kernel, dim3((unsigned)(N / rows), (unsigned)cols), dim3((unsigned)(64 * waves)), s, a);
     };
-    // up to 4096 rows a row block has a CU to itself and takes more waves; from 12288 on, 32-row blocks still
-    // give every CU work and read X half as often (16 x 14336 x 14336: 59 us, 69 with 16; 16 x 11008 x
-    // 4096: 15.6, 13.7 with 16)
-    const bool low = N <= 4096, high = N >= 12288;
+    // where there are at most 256 row blocks of 16, a block has a CU to itself and takes more waves; M <= 16: from
+    // 12288 rows on, 32-row blocks still give every CU work and read X half as often (16 x 14336 x 14336: 59 us, 69
+    // with 16; 16 x 11008 x 4096: 15.6, 13.7 with 16); M > 16: they do wherever there are more than 256 of 16
+    // (32 x 4224 x 14336: 25.1 us, 35 with 16 rows and four waves; 32 x 8192 x 14336 32.5 against 39, 32 x 11008 x
+    // 4096 19.8 against 20.8; 64 x 4096 x 4096 10.1 against 12.2)
     if (M <= 16) {
-      if (low) go(k_hybrid_few<1, 1, 16>, 16, 16);
-      else if (high) go(k_hybrid_few<2, 1, 8>, 32, 8);
+      if (N <= 4096) go(k_hybrid_few<1, 1, 16>, 16, 16);
+      else if (N >= 12288) go(k_hybrid_few<2, 1, 8>, 32, 8);
       else go(k_hybrid_few<1, 1, 8>, 16, 8);
-    } else if (M <= 32) {
-      if (low) go(k_hybrid_few<1, 2, 8>, 16, 8);
-      else if (high) go(k_hybrid_few<2, 2, 8>, 32, 8);
-      else go(k_hybrid_few<1, 2, 4>, 16, 4);
     } else {
-      go(k_hybrid_few<1, 4, 8>, 16, 8);
+      if (N * cols <= 4096) go(k_hybrid_few<1, 2, 8>, 16, 8);
+      else go(k_hybrid_few<2, 2, 8>, 32, 8);
     }
     return hipGetLastError() == hipSuccess ? SLIM_OK : SLIM_EDEVICE;
   }

@@ -78,8 +78,9 @@ def test_linear_odd_tile_rows(n, k, m):
     _check_product(Y, X, P.hybrid_weight(W, kinds))
 
 
-# The kernel for few rows: each of its row counts' edges, its three row-block shapes (N up to 4096, up to 12160,
-# beyond), chunk counts below, at and past one and two per wave, an odd last row of tiles.
+# The kernel for few rows: each of its row counts' edges, its row-block shapes (up to 16 rows: N up to 4096, up to
+# 12160, beyond; more: N times the halves of 32 rows up to 4096, beyond), an odd last row of tiles. 12288 x 640
+# gives its eight waves at most one chunk; the next test goes past that.
 @pytest.mark.parametrize("m", [1, 15, 16, 17, 32, 33, 64])
 @pytest.mark.parametrize("n,k,frac", [(128, 128, 0.5), (1152, 1152, 0.0), (4096, 2176, 0.7), (4224, 4224, 0.6),
                                       (12288, 640, 0.5)])
@@ -91,6 +92,62 @@ def test_linear_few_rows(n, k, m, frac):
     p = slim.pack_hybrid(dev(W), kinds)
     Y = host(slim.linear_hybrid(dev(X), p))
     _check_product(Y, X, P.hybrid_weight(W, kinds))
+
+
+# The 32-row blocks with more chunks than waves: a second chunk for one wave, two for each, and the third and fourth
+# of the pairs that are summed together.
+@pytest.mark.parametrize("m", [1, 16, 17, 32])
+@pytest.mark.parametrize("k", [1152, 2048, 3200])
+def test_linear_few_rows_long_chains(k, m):
+    n = 12288
+    print(f"hybrid few n={n} k={k} m={m}", flush=True)
+    W = _w(n, k, 8)
+    kinds = _kinds(n, k, 8, 0.5)
+    X = _x(m, k, 8)
+    p = slim.pack_hybrid(dev(W), kinds)
+    Y = host(slim.linear_hybrid(dev(X), p))
+    cols = np.unique(np.concatenate([synth.stream(8, "cols").choice(n, size=512, replace=False), np.arange(n - 64, n)]))
+    Wp = P.hybrid_weight(W.reshape(n // 128, 128, k)[np.unique(cols // 128)].reshape(-1, k), kinds[np.unique(cols // 128)])
+    at = np.searchsorted(np.unique(cols // 128), cols // 128) * 128 + cols % 128
+    _check_product(Y[:, cols], X, Wp[at])
+
+
+def _split_chain_error(X, W, tiles):
+    """Relative 2-norm error of X W^T where K is cut for about 512 blocks and every piece is one fp32 sum of exact
+    8-term products, one after another (two to a matrix instruction: about its roundings), as are the pieces: the
+    most accurate of the splits the GEMM considers, added up in the simplest order."""
+    m, k = X.shape
+    nch = k // 128
+    s = min(nch, -(-512 // tiles)) if tiles < 256 else 1
+    cps = -(-nch // s)
+    steps = (X.astype(np.float64).reshape(m, 1, k // 8, 8) * W.astype(np.float64).reshape(1, -1, k // 8, 8)).sum(-1)
+    total = np.zeros((m, W.shape[0]), dtype=np.float32)
+    for c in range(0, k // 8, 16 * cps):
+        acc = np.zeros_like(total)
+        for t in range(c, min(c + 16 * cps, k // 8)):
+            acc = (acc.astype(np.float64) + steps[:, :, t]).astype(np.float32)
+        total = total + acc
+    ref = X.astype(np.float64) @ W.astype(np.float64).T
+    return float(np.linalg.norm(total - ref) / np.linalg.norm(ref))
+
+
+# Long sums stay as accurate as K cut for 512 blocks: the kernel for few rows (both of its shapes for more than 16
+# rows). 1.15: the matrix instructions' own order of their terms, and the sample.
+@pytest.mark.parametrize("m,n,k", [(32, 4224, 14336), (32, 2176, 14336), (64, 4096, 4096), (64, 2048, 4096), (16, 4224, 14336)])
+def test_long_sums_stay_accurate(m, n, k):
+    print(f"hybrid accuracy m={m} n={n} k={k}", flush=True)
+    W = _w(n, k, 9)
+    X = _x(m, k, 9)
+    p = slim.pack_hybrid(dev(W), np.zeros((n // 128, k // 128), dtype=np.uint8))
+    Y = host(slim.linear_hybrid(dev(X), p))
+    rows = np.sort(synth.stream(9, "rows").choice(m, size=16, replace=False))
+    cols = np.sort(synth.stream(9, "cols").choice(n, size=96, replace=False))
+    Xs, Ws = X[rows], P.fp16_rne(W[cols])
+    ref = Xs.astype(np.float64) @ Ws.astype(np.float64).T
+    err = float(np.linalg.norm(Y[np.ix_(rows, cols)] - ref) / np.linalg.norm(ref))
+    split = _split_chain_error(Xs, Ws, -(-n // 256) * -(-m // 128))
+    print(f"error {err:.3e}, of the splits for 512 blocks {split:.3e}", flush=True)
+    assert err <= 1.15 * split
 
 
 # Split counts of the tile GEMM and its reduction: one, a few, and one per chunk; a shorter last split
