@@ -530,25 +530,32 @@ k_hybrid_few(HybridArgs g) {
   }
 }
 
-// Sums of the split partials, in an order fixed by the split count: 64 outputs (of four values) per block, the
-// splits over four groups of threads with four loads in flight each, the groups' sums added through LDS. One
-// thread per output walking all splits waited for every load in turn (112 splits: 28 us).
+// Sums of the split partials, in an order fixed by the sizes: 256 / G outputs (of four values) per block, the splits
+// over G groups of threads with four loads in flight each, the groups' sums added through LDS. One thread per output
+// walking all splits waited for every load in turn (112 splits: 28 us).
+template <int G>
 __global__ void __launch_bounds__(kHThreads)
 k_hybrid_reduce(const float* __restrict__ part, int splits, int64_t count4, float* __restrict__ Y) {
-  __shared__ f4_t sums[3][64];
-  const int lane = threadIdx.x & 63, grp = threadIdx.x >> 6;
-  const int64_t i = (int64_t)blockIdx.x * 64 + lane;
+  constexpr int kOut = kHThreads / G;
+  __shared__ f4_t sums[G > 1 ? G - 1 : 1][kOut];
+  const int at = threadIdx.x % kOut, grp = threadIdx.x / kOut;
+  const int64_t i = (int64_t)blockIdx.x * kOut + at;
   const f4_t* p = reinterpret_cast<const f4_t*>(part) + (i < count4 ? i : count4 - 1);
   f4_t s = f4_t{0.f, 0.f, 0.f, 0.f};
   int z = grp;
-  for (; z + 12 < splits; z += 16) {
-    const f4_t v0 = p[z * count4], v1 = p[(z + 4) * count4], v2 = p[(z + 8) * count4], v3 = p[(z + 12) * count4];
+  for (; z + 3 * G < splits; z += 4 * G) {
+    const f4_t v0 = p[z * count4], v1 = p[(z + G) * count4], v2 = p[(z + 2 * G) * count4], v3 = p[(z + 3 * G) * count4];
     s += (v0 + v1) + (v2 + v3);
   }
-  for (; z < splits; z += 4) s += p[z * count4];
-  if (grp > 0) sums[grp - 1][lane] = s;
-  __syncthreads();
-  if (grp == 0 && i < count4) reinterpret_cast<f4_t*>(Y)[i] = (s + sums[0][lane]) + (sums[1][lane] + sums[2][lane]);
+  for (; z < splits; z += G) s += p[z * count4];
+  if constexpr (G > 1) {
+    if (grp > 0) sums[grp - 1][at] = s;
+    __syncthreads();
+    if (grp > 0) return;
+    static_assert(G == 4, "the groups' sums are added two by two");
+    s = (s + sums[0][at]) + (sums[1][at] + sums[2][at]);
+  }
+  if (i < count4) reinterpret_cast<f4_t*>(Y)[i] = s;
 }
 
 // Rows served by k_hybrid_few. Its weights are read once whatever M is, and X once per row block, so it is the
@@ -570,7 +577,12 @@ struct HybridPlan {
   size_t ws;
 };
 
-// Splits of K: the count of least estimated time. A block takes t0 = 4.5 us and 2 us per chunk (fitted at 64
+// Splits of K: the count of least estimated time of those that sum as accurately as the most that are considered, s0
+// (no more than two rounds of blocks), added up one after another. A split's sum makes up to eight roundings per
+// chunk, each about 1.6 times (in variance, measured) as heavy as an addition of the partials, of which the
+// reduction's order leaves at most about s / 16 + 8 in a chain: 13 chunks + s / 16 + 8 <= 13 chunks0 + s0. With the time
+// alone 64 x 14336 x 14336 took four splits instead of ten, 80 us instead of 92 and 3.3e-7 from 64 bits instead
+// of 2.2e-7. A block takes t0 = 4.5 us and 2 us per chunk (fitted at 64
 // rows of 4096 x 4096 in 1 to 32 splits, 65 to 13 us a launch; with 256 blocks at work a chunk's 45 KB each
 // make 5.8 TB/s), blocks run 256 at a time with the last split's shorter ones last, and the partials cost
 // the reduction's launch, 3 us, and their writing and reading at 7 TB/s.
@@ -587,9 +599,11 @@ HybridPlan hybrid_plan(int64_t M, int64_t N, int64_t K) {
   if (most > chunks) most = chunks;
   double best = 0;
   const uint32_t nch = (uint32_t)chunks;               // at most 256
+  const uint32_t cps0 = (nch + (uint32_t)most - 1) / (uint32_t)most, s0 = (nch + cps0 - 1) / cps0;
   for (uint32_t s = 1; s <= (uint32_t)most; ++s) {
     const uint32_t cps = (nch + s - 1) / s;
     if (cps * (s - 1) >= nch) continue;                 // fewer splits of as many chunks
+    if (cps > cps0 && 13 * cps + s / 16 + 8 > 13 * cps0 + s0) continue;
     const double full = 4.5 + 2.0 * cps, last = 4.5 + 2.0 * (nch - (s - 1) * cps);
     const int64_t nfull = p.tiles * (s - 1), busy = nfull % 256, idle = 256 - busy;
     // whole rounds, then the busy blocks' end or the last split's, in as many rounds as the idle CUs need
@@ -597,7 +611,7 @@ HybridPlan hybrid_plan(int64_t M, int64_t N, int64_t K) {
     const double ends = last * (double)((p.tiles + idle - 1) / idle), both = (busy ? full : 0) + last * (double)((p.tiles + 255) / 256);
     t += busy && ends < full ? full : (ends < both ? ends : both);
     if (s > 1) t += 3.0 + (double)s * (double)M * (double)N * (8 / 7e6);
-    if (s == 1 || t < best) {
+    if (best == 0 || t < best) {
       best = t;
       p.splits = s;
       p.chunks_per_split = cps;
@@ -723,8 +737,14 @@ extern "C" int slim_linear_hybrid(const void* X, int64_t M, int64_t N, int64_t K
   if (p.splits > 1) {
     const int64_t count4 = M * N / 4;
     SlimKernelTimer timer("hybrid_reduce", s);
-    SLIM_LAUNCH(timer, k_hybrid_reduce, dim3((unsigned)((count4 + 63) / 64)), dim3(kHThreads), s,
-                (const float*)static_cast<float*>(ws), (int)p.splits, count4, Y);
+    auto reduce = [&](auto kernel, int64_t outs) {
+      SLIM_LAUNCH(timer, kernel, dim3((unsigned)((count4 + outs - 1) / outs)), dim3(kHThreads), s,
+                  (const float*)static_cast<float*>(ws), (int)p.splits, count4, Y);
+    };
+    // from 512 blocks of one thread per output on, four threads for each only add blocks (128 x 8192 x 2048, 16
+    // splits: 36.2 us against 39.0; below it 120 x 512 x 14336: 21.7 against 18.5)
+    if (count4 >= 512 * kHThreads) reduce(k_hybrid_reduce<1>, kHThreads);
+    else reduce(k_hybrid_reduce<4>, kHThreads / 4);
   }
   return hipGetLastError() == hipSuccess ? SLIM_OK : SLIM_EDEVICE;
 }

@@ -233,3 +233,23 @@ def test_sizes_that_fit_the_noalloc_scratch_on_512_row_tiles_still_fit():
         if base <= lim:
             assert now <= lim, (m, n, k, r, base, now)
     assert near > 1000
+
+
+def test_hybrid_splits_are_as_accurate_as_the_most_considered():
+    # roundings of a split's sum (13 per chunk, in those of an addition) and of the reduction's chain, against the
+    # split for 512 blocks added up one after another, whose workspace is also never exceeded
+    import random
+    rng = random.Random(7)
+    fewer = 0
+    for _ in range(5000):
+        n, k, m = 128 * rng.randint(1, 112), 128 * rng.randint(1, 112), rng.randint(65, 2048)
+        nch, tiles = k // 128, -(-n // 256) * -(-m // 128)
+        most = min(nch, -(-512 // tiles)) if tiles < 256 else 1
+        cps0 = -(-nch // most)
+        s0 = -(-nch // cps0)
+        s = max(1, slim.slim_linear_hybrid_workspace(m, n, k) // (4 * m * n))
+        cps = -(-nch // s)
+        assert s <= s0, (m, n, k)
+        assert cps <= cps0 or 13 * cps + s // 16 + 8 <= 13 * cps0 + s0, (m, n, k, s, s0)
+        fewer += s < s0
+    assert fewer > 100
