@@ -709,7 +709,7 @@ SLIM_DEV void tile_body(const LayerArgs& a) {
   const int64_t rt = band * kb + q % rb, ct = q / rb;
   const int64_t row0 = rt * kTR, m0 = ct * kTC;
   const int64_t wrow0 = row0 + 64 * wave;
-  const int64_t nch = a.red / 128;
+  const int nch = (int)(a.red / 128);        // at most 2^16
 
   // Addresses. Rows past the matrix (or past M) get offsets at or beyond their resource's extent and
   // read as zero; their results are not stored. The uniform chunk offset only ever moves a valid row
@@ -727,9 +727,9 @@ SLIM_DEV void tile_body(const LayerArgs& a) {
   const uint32_t d0 = (uint32_t)(grow0 - 16 * wblk) + 32u * (uint32_t)fbase, snch = 16u * (uint32_t)nch;
   auto rel_slot = [&](uint32_t d) { return (d >> 4) * snch + (d & 15u); };
   const uint32_t fstep = 1024u * (uint32_t)nch;
-  const uint32_t co0 = rel_slot(d0 + (uint32_t)l32) * 32u + 16u * ha;           // codes: the wave's fragment 0
-  const uint32_t mo0 = rel_slot(d0 + (uint32_t)lane) * 16u;                     // index words: the wave's 64 rows
-  const uint32_t so0 = rel_slot(d0 - 32u * (uint32_t)fbase + 2u * (uint32_t)lane) * 2u;   // scales: group rows 2 L, 2 L + 1
+  uint32_t co = rel_slot(d0 + (uint32_t)l32) * 32u + 16u * ha;            // codes: the wave's fragment 0
+  uint32_t mo = rel_slot(d0 + (uint32_t)lane) * 16u;                      // index words: the wave's 64 rows
+  uint32_t so = rel_slot(d0 - 32u * (uint32_t)fbase + 2u * (uint32_t)lane) * 2u;   // scales: group rows 2 L, 2 L + 1
 
   // activation chunk c -> stage c % kStagesX: wave w writes rows R w .. R w + R - 1 (R = kActRows),
   // four per load (lane L: row + L / 16, LDS column slot L % 16 holding column
@@ -739,13 +739,13 @@ SLIM_DEV void tile_body(const LayerArgs& a) {
   const int lrow = lane >> 4, lslot = lane & 15;
   const int64_t brows = a.M - m0 < kTC ? a.M - m0 : kTC;
   const rsrc_t rx = make_rsrc(a.act16 + m0 * a.red, brows * a.red * 2);    // the block's activation rows
-  const uint32_t xo0 = (uint32_t)(Sh::kActRows * wave + lrow) * (uint32_t)a.red * 2u + 16u * (uint32_t)(lslot ^ lrow);
+  uint32_t xo = (uint32_t)(Sh::kActRows * wave + lrow) * (uint32_t)a.red * 2u + 16u * (uint32_t)(lslot ^ lrow);
   const uint32_t xstep = 8u * (uint32_t)a.red;
   const rsrc_t rg = make_rsrc(a.scales + (16 * wblk / 128) * a.red, a.red * 2);   // backward: the group's scale row
 
   // direct load i of a chunk's words (codes, codes, index words, scales) into stage z
-  auto dma_word = [&](int64_t c, int z, int i, uint32_t co, uint32_t mo, uint32_t so) {
-    const int cc = (int)clamp_hi(c, nch - 1);
+  auto dma_word = [&](int c, int z, int i, uint32_t co, uint32_t mo, uint32_t so) {
+    const int cc = c < nch ? c : nch - 1;
     uint8_t* W = lds + Sh::kWBase + (uint32_t)z * Sh::kW;
     if (i < 2)
       __builtin_amdgcn_raw_ptr_buffer_load_lds(rc, (lds_ptr_t)(W + 1024 * (4 * grp + fbase + i)), 16, co + i * fstep, 512 * cc, 0, 0);
@@ -756,8 +756,8 @@ SLIM_DEV void tile_body(const LayerArgs& a) {
   };
   // direct load i of a chunk's activations (the last one in the backward: the group's scale row
   // s16[n, g] of this chunk, four copies) into stage z
-  auto dma_act = [&](int64_t c, int z, int i, uint32_t xo) {
-    const int cc = (int)clamp_hi(c, nch - 1);
+  auto dma_act = [&](int c, int z, int i, uint32_t xo) {
+    const int cc = c < nch ? c : nch - 1;
     if (i < Sh::kActLoads)
       __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (lds_ptr_t)(lds + (uint32_t)z * Sh::kX + (uint32_t)(Sh::kActRows * wave + 4 * i) * 256u), 16,
                                                (xo ^ (16u * ((uint32_t)(Sh::kActRows * wave + 4 * i) & 15u))) + (uint32_t)i * xstep,
@@ -812,7 +812,7 @@ SLIM_DEV void tile_body(const LayerArgs& a) {
   // and that ^ 8 (high half): with bo = 256 (L % 32) + 16 ((L % 16) ^ (L / 32)) at bytes
   // 8192 fm + (bo ^ 32 st) and 8192 fm + (bo ^ (32 st + 128)) of the stage; the third stage of 24 KiB lies
   // past the 16-bit offset of a DS instruction and gets its addresses by an addition
-  const uint32_t bo0 = 256u * (uint32_t)l32 + 16u * (uint32_t)((lane & 15) ^ ha);
+  uint32_t bo = 256u * (uint32_t)l32 + 16u * (uint32_t)((lane & 15) ^ ha);
   const uint32_t gso = lb + Sh::kSBase + 1024u * (uint32_t)grp + 16u * (uint32_t)ha;    // backward: the scale row
   struct Bfrag {
     u32x4_t lo, hi;
@@ -848,14 +848,14 @@ SLIM_DEV void tile_body(const LayerArgs& a) {
   h8_t aq[2][kFn];
 
 #pragma unroll
-  for (int i = 0; i < Sh::kAct; ++i) dma_act(0, 0, i, xo0);
+  for (int i = 0; i < Sh::kAct; ++i) dma_act(0, 0, i, xo);
 #pragma unroll
-  for (int i = 0; i < Sh::kWords; ++i) dma_word(0, 0, i, co0, mo0, so0);
+  for (int i = 0; i < Sh::kWords; ++i) dma_word(0, 0, i, co, mo, so);
   if (Sh::kAhead == 2)
 #pragma unroll
-    for (int i = 0; i < Sh::kAct; ++i) dma_act(1, 1, i, xo0);
+    for (int i = 0; i < Sh::kAct; ++i) dma_act(1, 1, i, xo);
 #pragma unroll
-  for (int i = 0; i < Sh::kWords; ++i) dma_word(1, 1, i, co0, mo0, so0);
+  for (int i = 0; i < Sh::kWords; ++i) dma_word(1, 1, i, co, mo, so);
   // chunk 0 has landed once only chunk 1's loads are outstanding; the other waves brought in part of its
   // activations. The barriers are bare instructions: the builtin would also make this wave wait for every
   // direct load in flight.
@@ -866,10 +866,10 @@ SLIM_DEV void tile_body(const LayerArgs& a) {
 #pragma unroll
   for (int fn = 0; fn < kFn; ++fn) aq[0][fn] = dequant(tw[0], 0, fn);
   if constexpr (BWD) read_s(ic<0>{}, ic<0>{}, sq[0]);
-  read_b(ic<0>{}, ic<0>{}, ic<0>{}, bo0, bq[0]);
-  read_b(ic<0>{}, ic<0>{}, ic<1>{}, bo0, bq[1]);
-  read_b(ic<0>{}, ic<0>{}, ic<2>{}, bo0, bq[2]);
-  if constexpr (kFm == 4) read_b(ic<0>{}, ic<0>{}, ic<3>{}, bo0, bq[3]);
+  read_b(ic<0>{}, ic<0>{}, ic<0>{}, bo, bq[0]);
+  read_b(ic<0>{}, ic<0>{}, ic<1>{}, bo, bq[1]);
+  read_b(ic<0>{}, ic<0>{}, ic<2>{}, bo, bq[2]);
+  if constexpr (kFm == 4) read_b(ic<0>{}, ic<0>{}, ic<3>{}, bo, bq[3]);
   auto landed = [&]() {
     asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(bq[0].lo), "+v"(bq[0].hi), "+v"(bq[1].lo), "+v"(bq[1].hi), "+v"(bq[2].lo), "+v"(bq[2].hi));
     if constexpr (kFm == 4) asm volatile("" : "+v"(bq[kFm - 1].lo), "+v"(bq[kFm - 1].hi));
@@ -889,14 +889,15 @@ SLIM_DEV void tile_body(const LayerArgs& a) {
   // landed; the next chunk's first fragments are read from then on (the last of them into registers of
   // their own) and waited for at the chunk's end, so that no read is in flight across the loop's edges,
   // where the register allocator may move values.
-  auto chunk = [&](int64_t c, auto xc, auto zc, auto pc) {
+  auto chunk = [&](int c, auto xc, auto zc, auto pc) {
     constexpr int xs = decltype(xc)::value, z = decltype(zc)::value, p = decltype(pc)::value;
     constexpr int xn = (xs + 1) % kStagesX, zn = (z + 1) % 3;
     const Words& cur = tw[p];
     Words& nxt = tw[p ^ 1];
-    // this chunk's copies of the base offsets (opaque, so nothing derived from them is hoisted)
-    uint32_t xo = xo0, co = co0, mo = mo0, so = so0, bo = bo0;
-    asm volatile("" : "+v"(xo), "+v"(co), "+v"(mo), "+v"(so), "+v"(bo));
+    // the base offsets, opaque in place, so that nothing derived from them is hoisted out of the chunk (opaque copies
+    // hold five more registers: the backward's 128-wide tile then spills, and the reload waits for every load in flight)
+    asm volatile("" : "+v"(xo), "+v"(co), "+v"(mo), "+v"(bo));
+    if constexpr (!BWD) asm volatile("" : "+v"(so));
     auto step = [&](auto stc) {
       constexpr int st = decltype(stc)::value;
       // reads outstanding after a fragment's own, on arrival at its MFMAs
@@ -985,7 +986,7 @@ SLIM_DEV void tile_body(const LayerArgs& a) {
     step(ic<2>{});
     step(ic<3>{});
   };
-  int64_t c0 = 0;
+  int c0 = 0;
   for (; c0 + 6 <= nch; c0 += 6) {
     chunk(c0, ic<0>{}, ic<0>{}, ic<0>{});
     chunk(c0 + 1, ic<1>{}, ic<1>{}, ic<1>{});
