@@ -72,17 +72,31 @@ int64_t adapter_slices(int64_t at, int64_t red) {
 bool mid_plan(bool bwd, int64_t M, int64_t rows, int64_t red, int64_t r, SlimPlan* q) {
   const int64_t nch = red / 128, big = cdiv(rows, 256) * cdiv(M, 128);
   // With about as many 256 x 128 tiles as CUs the 512-row tiles win (half the LDS and direct-load bytes per
-  // weight row; with an adapter also no fp32 partials through memory). Forward with an adapter: 11008 x
-  // 4096, M 512 (172 tiles) 69 against 76 us, M 700 (258) 90 against 79, 4096 x 4096, M 1500 (192) 84
-  // against 83; longer reductions pay for the partials longer (28672 x 8192, M 200 (224) 116 against 124).
-  // Backward with an adapter: 5120 x 13824, M 333 (162) 94 against 101, M 512 (216) 111 against 107, 4096 x
-  // 4096, M 1500 (192) 100 against 91. Without an adapter one whole round is still better in the forward
-  // (4096 x 4096, M 2048: 53 against 57), not in the backward, which scales every operand fragment (65
-  // against 64; M 1500: 56 against 60).
-  const int64_t limit = r == 0 ? (bwd ? 224 : 256) : (bwd ? 164 : (red >= 8192 ? 224 : 180));
+  // weight row; with an adapter also no fp32 partials through memory): limits from both plans' times on 750 sizes of
+  // 512 to 28672 rows, reductions of 512 to 14336 and M 33 to 8192; past them the middle path lost, below them no
+  // call lost more than 2 %. Without an adapter one whole round is still better in the forward (4096 x 4096, M 2048:
+  // 55 us against 58; 8192 x 8192, M 1024: 94 against 96), less of one in the backward, which scales every operand
+  // fragment (7296 rows, reduction 13824, M 663: 147 against 162), unless M is larger than the rows: then each
+  // block's output is the larger part, for short reductions most of all (1024 x 2048, M 8192: 58 against 47; 1024 x
+  // 640, M 7963: 40 % over). With an adapter: forward 11008 x 4096, M 512 (172 tiles) 67 against 76, 3328 x 1280, M
+  // 2246 (234) 53 against 48; longer reductions pay for the partials longer (28672 x 8192, M 200 (224) 116 against
+  // 124) unless those are many (2048 x 9216, M 3500 (224) 157 against 151). Backward 5120 x 13824, M 333 (162) 93
+  // against 102, 2944 rows, reduction 3584, M 2004 (192) 90 against 82.
+  int64_t limit;
+  if (r == 0) {
+    if (M <= rows) limit = bwd ? 224 : 256;
+    else if (!bwd && red > 4096) limit = 256;
+    else limit = nch > (bwd ? 9 : 6) ? (bwd ? 200 : 190) : 140;
+  } else if (bwd) {
+    limit = 164;
+  } else {
+    limit = nch <= 4 ? 128 : (red >= 8192 && M <= rows ? 224 : 180);
+  }
   if (big > limit) return false;
   if (r > 0 && cdiv(M, 64) * cdiv(r, 128) > (int64_t)kCounterSlots) return false;
   double best = 0;
+  int cols = 0, slices = 1;
+  int64_t chunks = nch;
   for (int tc = 64; tc <= 128; tc += 64) {
     const int64_t R = cdiv(rows, 2 * tc), C = cdiv(M, tc);
     for (int64_t s = 1; s <= 8 && (s == 1 || nch >= 4 * s); ++s) {
@@ -97,22 +111,32 @@ bool mid_plan(bool bwd, int64_t M, int64_t rows, int64_t red, int64_t r, SlimPla
       if (split > 1 || r > 0) t += split * M * rows * 8 / 4e6;
       if (best == 0 || t < best) {
         best = t;
-        q->sp_cols_tile = tc;
-        q->sp_split = (int)split;
-        q->sp_chunks_per_split = per;
+        cols = tc;
+        slices = (int)split;
+        chunks = per;
       }
     }
   }
-  q->mid = true;
-  q->sp_rows_tile = 2 * q->sp_cols_tile;
-  q->sp_row_tiles = cdiv(rows, q->sp_rows_tile);
-  q->sp_col_tiles = cdiv(M, q->sp_cols_tile);
   if (r > 0) {
-    q->ad_tiles_m = (int)cdiv(M, q->sp_cols_tile);
+    const int64_t at = cdiv(M, cols) * cdiv(r, 128), ad_slice = cdiv(cdiv(red, adapter_slices(at, red)), 64) * 64;
+    // where the adapter's units and one round of 256 x 128 tiles are more blocks than CUs (by more than a few, where
+    // the weights are the larger operand), they take two rounds (backward 4096 x 4096, r 384, M 1280: 93 us against
+    // 85; forward 2432 x 3968, r 224, M 2250: 81 against 76), and the shortest reductions do not pay for the backward's
+    // finish (16640 x 640, r 64, M 231: 34.8 against 33.8)
+    const bool two = cols == 128 && slices == 1 && big + at * cdiv(red, ad_slice) > (M > rows ? 256 : 272);
+    if (bwd ? two || (cols == 128 && nch <= 5 && big > 128) : two && red <= 8192 && 2 * M > rows && big > 150) return false;
+    q->ad_tiles_m = (int)cdiv(M, cols);
     q->ad_tiles_j = (int)cdiv(r, 128);
-    q->ad_slice = cdiv(cdiv(red, adapter_slices((int64_t)q->ad_tiles_m * q->ad_tiles_j, red)), 64) * 64;
-    q->ad_split = (int)cdiv(red, q->ad_slice);
+    q->ad_slice = ad_slice;
+    q->ad_split = (int)cdiv(red, ad_slice);
   }
+  q->mid = true;
+  q->sp_cols_tile = cols;
+  q->sp_rows_tile = 2 * cols;
+  q->sp_row_tiles = cdiv(rows, 2 * cols);
+  q->sp_col_tiles = cdiv(M, cols);
+  q->sp_split = slices;
+  q->sp_chunks_per_split = chunks;
   return true;
 }
 
