@@ -68,8 +68,8 @@ int64_t adapter_slices(int64_t at, int64_t red) {
 
 // The middle path, where 512-row tiles are too few for the chip: 128 x 64 tiles, two blocks per CU, or
 // 256 x 128, one, over S slices of the reduction, whichever the cost below favours. Returns false where the
-// 512-row tiles are the better choice.
-bool mid_plan(bool bwd, int64_t M, int64_t rows, int64_t red, int64_t r, SlimPlan* q) {
+// 512-row tiles are the better choice. `most`: bytes the partials and the fp16 activations may take.
+bool mid_plan(bool bwd, int64_t M, int64_t rows, int64_t red, int64_t r, int64_t most, SlimPlan* q) {
   const int64_t nch = red / 128, big = cdiv(rows, 256) * cdiv(M, 128);
   // With about as many 256 x 128 tiles as CUs the 512-row tiles win (half the LDS and direct-load bytes per
   // weight row; with an adapter also no fp32 partials through memory): limits from both plans' times on 750 sizes of
@@ -101,8 +101,7 @@ bool mid_plan(bool bwd, int64_t M, int64_t rows, int64_t red, int64_t r, SlimPla
     const int64_t R = cdiv(rows, 2 * tc), C = cdiv(M, tc);
     for (int64_t s = 1; s <= 8 && (s == 1 || nch >= 4 * s); ++s) {
       const int64_t per = cdiv(nch, s), split = cdiv(nch, per), blocks = R * C * split;
-      // the partials, beside the fp16 activations, stay within the no-allocation entry point's scratch
-      if (s > 1 && split * R * C * 2 * tc * tc * 4 + 2 * M * red > (int64_t)SLIM_NOALLOC_SCRATCH_BYTES - (8 << 20)) break;
+      if (s > 1 && split * R * C * 2 * tc * tc * 4 + 2 * M * red > most) break;
       // microseconds per chunk: a lone 128 x 64 block on a CU 0.40, two 0.75, a 256 x 128 block 1.15;
       // the adapter's chain beside them takes at least about 7
       double t = per * (tc == 64 ? (blocks <= 256 ? 0.40 : 0.75 * cdiv(blocks, 512)) : 1.15 * cdiv(blocks, 256));
@@ -141,8 +140,8 @@ bool mid_plan(bool bwd, int64_t M, int64_t rows, int64_t red, int64_t r, SlimPla
 }
 
 // One plan. `rows512` (M > 32): 512-row tiles and the kernels of k_adapter_gemm; otherwise the middle path or its
-// first-product units where they are the faster ones.
-int plan_kernels(bool bwd, int64_t M, int64_t N, int64_t K, int64_t r, bool rows512, SlimPlan* p) {
+// first-product units where they are the faster ones, `most` as above.
+int plan_kernels(bool bwd, int64_t M, int64_t N, int64_t K, int64_t r, bool rows512, int64_t most, SlimPlan* p) {
   if (M < 1 || N < 16 || K < 128 || M >= kMaxDim || N >= kMaxDim || K >= kMaxDim) return SLIM_ESHAPE;
   if (N % 16 || K % 128 || r < 0 || r % 16 || r >= kMaxDim) return SLIM_ESHAPE;
   if (bwd && N % 128) return SLIM_ESHAPE;
@@ -194,7 +193,7 @@ int plan_kernels(bool bwd, int64_t M, int64_t N, int64_t K, int64_t r, bool rows
     if (red > kMaxLargeRed || cdiv(M, 32) * 32 * r >= kMaxTiledElems || cdiv(rows, 32) * 32 * r >= kMaxTiledElems)
       return SLIM_EUNSUPPORTED;
     q.decode = false;
-    if (!rows512 && mid_plan(bwd, M, rows, red, r, &q)) {
+    if (!rows512 && mid_plan(bwd, M, rows, red, r, most, &q)) {
       if (q.sp_split > 1 || r > 0)
         ypart_bytes = (size_t)q.sp_split * (size_t)(q.sp_row_tiles * q.sp_rows_tile) * (size_t)(q.sp_col_tiles * q.sp_cols_tile) * 4;
       if (q.ad_split > 1) {
@@ -297,13 +296,19 @@ int plan_kernels(bool bwd, int64_t M, int64_t N, int64_t K, int64_t r, bool rows
 // most rows may be short for it with fewer. The query is the larger of the two sizes, so that it also covers every
 // smaller M that the 512-row plans' sizes cover.
 int slim_make_plan(bool bwd, int64_t M, int64_t N, int64_t K, int64_t r, size_t ws_bytes, SlimPlan* p) {
-  int st = plan_kernels(bwd, M, N, K, r, true, p);
+  int st = plan_kernels(bwd, M, N, K, r, true, 0, p);
   if (st != SLIM_OK || p->decode) return st;
+  // Sizes that fit the no-allocation entry point's scratch on either plan keep fitting (it sums in the order of the
+  // calls with a workspace): there the partials leave room for the rest. Past it on both the scratch says nothing.
+  constexpr size_t scratch = SLIM_NOALLOC_SCRATCH_BYTES;
   SlimPlan q;
-  st = plan_kernels(bwd, M, N, K, r, false, &q);
+  st = plan_kernels(bwd, M, N, K, r, false, (int64_t)scratch - (8 << 20), &q);
   if (st != SLIM_OK) return st;
-  // sizes that fit the no-allocation entry point's scratch on the 512-row tiles keep fitting
-  if ((q.mid || q.ad_tn) && q.total > (size_t)SLIM_NOALLOC_SCRATCH_BYTES) return SLIM_OK;
+  if ((q.mid || q.ad_tn) && q.total > scratch) {
+    if (p->total <= scratch) return SLIM_OK;
+    st = plan_kernels(bwd, M, N, K, r, false, INT64_MAX, &q);
+    if (st != SLIM_OK) return st;
+  }
   q.query = p->query = std::max(p->total, q.total);
   if (q.total <= ws_bytes) *p = q;
   return SLIM_OK;

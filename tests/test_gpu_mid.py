@@ -32,6 +32,7 @@ def _counters_zero(ws):
     (8208, 1152, 0, 700, "fp16"),    # 256 x 128 tiles, no partials
     (8208, 1152, 160, 300, "bf16"),  # 256 x 128 tiles with the adapter
     (512, 512, 32, 3000, "bf16"),    # many column tiles
+    (2048, 14336, 192, 2048, "bf16"),   # past the library's own scratch: 256 x 128 tiles, two slices, 105 MB
 ])
 def test_forward_edges(n, k, r, m, xdtype):
     print(f"mid fwd n={n} k={k} r={r} m={m} {xdtype}", flush=True)
@@ -56,6 +57,7 @@ def test_forward_edges(n, k, r, m, xdtype):
     (4096, 1024, 272, 200, "bf16"),
     (1152, 8192, 0, 700, "bf16"),    # 256 x 128 tiles (whole scale groups per tile half), no partials
     (1152, 8192, 96, 300, "bf16"),
+    (8192, 512, 32, 8192, "bf16"),   # past the library's own scratch: 256 x 128 tiles, two slices
 ])
 def test_backward_edges(n, k, r, m, xdtype):
     print(f"mid bwd n={n} k={k} r={r} m={m} {xdtype}", flush=True)

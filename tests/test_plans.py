@@ -1,6 +1,7 @@
 """The choice between the middle path and the 512-row tiles."""
 import pytest
 
+from paper_2608_24070_amd import slim
 from tests.plans import plan
 
 
@@ -22,3 +23,20 @@ from tests.plans import plan
 def test_middle_path_where_it_is_faster(kind, m, rows, red, r, mid):
     n, k = (red, rows) if kind == "dx" else (rows, red)
     assert plan(kind, m, n, k, r).mid == mid
+
+
+# Sizes past the no-allocation entry point's scratch on the 512-row tiles too: it does not choose between the plans
+@pytest.mark.parametrize("kind,m,rows,red,r", [
+    ("fwd", 4096, 512, 14336, 0), ("fwd", 2048, 2048, 14336, 192), ("fwd", 3000, 1024, 13824, 96),
+    ("dx", 4096, 512, 14336, 0), ("dx", 2048, 2048, 14336, 192), ("fwd", 2048, 5120, 13824, 512)])
+def test_scratch_decides_nothing_past_it(kind, m, rows, red, r):
+    n, k = (red, rows) if kind == "dx" else (rows, red)
+    p = plan(kind, m, n, k, r)
+    assert plan(kind, m, n, k, r, 0).total > slim.SLIM_NOALLOC_SCRATCH_BYTES
+    assert p.mid or p.ad_tn
+
+
+def test_scratch_keeps_what_fits_it():
+    # the 512-row tiles fit the scratch, the middle path's partials do not
+    p = plan("fwd", 1000, 4096, 11008, 384)
+    assert not p.mid and p.total <= slim.SLIM_NOALLOC_SCRATCH_BYTES
