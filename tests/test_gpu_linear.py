@@ -68,13 +68,14 @@ def test_small_m_multi_fragment(m):
 
 
 @pytest.mark.parametrize("m,r", [(65, 32), (200, 16), (256, 0), (300, 48), (40, 80)])
-def test_tile_kernel_ragged(m, r):
+def test_large_m_ragged(m, r):
+    # small layers past 32 rows: the middle path (tests/test_gpu_tile.py has the 512-row tiles)
     _fwd_case(768, 1024, r, m, name="ragged")
 
 
 @pytest.mark.parametrize("k,m", [(128, 100), (256, 97), (384, 130)])
-def test_tile_kernel_short_reduction(k, m):
-    # one to three 128-wide chunks: the tile kernel's prologue and remainder paths alone
+def test_large_m_short_reduction(k, m):
+    # one to three 128-wide chunks on the middle path
     _fwd_case(528, k, 16, m, name="shortk")
 
 
@@ -128,7 +129,7 @@ def test_tile_kernel_eight_waves_ragged_rows():
 def test_tile_epilogue_rank_groups(n, k, r, m):
     # the epilogue's adapter product takes tm through LDS in groups of eight 16-rank steps, one
     # activation stage per group: 512 x 128 tiles (two stages) with three groups, the last one whole
-    # (r 384) or of one step (r 272), and 512 x 96 tiles (three stages) with r 272
+    # (r 384) or of one step (r 272); the last case's rank is the middle path's finish
     rows = np.unique(np.concatenate([synth.stream(10, "rows").choice(n, size=min(n, 256), replace=False),
                                      np.arange(n - 16, n)]))
     ms = np.unique(np.concatenate([synth.stream(10, "ms").choice(m, size=40, replace=False), np.arange(m - 8, m)]))
@@ -137,10 +138,9 @@ def test_tile_epilogue_rank_groups(n, k, r, m):
 
 @pytest.mark.parametrize("n,k,r,m", [(256, 33024, 512, 1900), (128, 16384, 512, 4096), (128, 2048, 512, 32768)])
 def test_adapter_gemm_wide_tiles(n, k, r, m):
-    # the 256 x 256 adapter GEMM takes shapes whose 256 x 256 tiles times reduction splits of at least
-    # 2048 fill 256 blocks: a ragged last m tile (M = 1900, 16 tiles) over 16 splits whose last one is
-    # short (reduction 33024 in slices of 2080), 32 tiles over 8 splits of exactly 2048, and 256 tiles
-    # with no split (T written in fp16 by the GEMM itself)
+    # the 256 x 256 adapter GEMM, before 512-row tiles, takes shapes whose 256 x 256 tiles times reduction splits of
+    # at least 2048 fill 256 blocks: the last case is 256 tiles with no split (T written in fp16 by the GEMM itself;
+    # tests/test_gpu_tile.py has the splits); the first two are long reductions and many rows on the middle path
     ms = np.unique(np.concatenate([synth.stream(8, "ms").choice(m, size=40, replace=False), np.arange(m - 8, m)]))
     _fwd_case(n, k, r, m, ms=ms, name="adwide")
 
@@ -224,9 +224,8 @@ def _bwd_case(n, k, r, m, seed=0, ks=None, ms=None, name="bwd", dydtype="bf16", 
         assert_close(dX[np.ix_(ms, np.arange(128 * g, 128 * g + 128))], ref, f"bwd group {g}")
 
 
-def test_tile_kernel_exact_tiles():
-    # rows and columns that fill whole 512 x 96 tiles: no ragged edge anywhere (two row tiles, four
-    # column tiles, a reduction of eight chunks)
+def test_large_m_exact_tiles():
+    # rows and columns that fill whole tiles of the middle path: no ragged edge anywhere
     _fwd_case(1024, 1024, 64, 384, name="exact")
 
 
@@ -263,9 +262,9 @@ def test_bwd_wide_tiles_ragged_m():
     _bwd_case(2048, 11008, 48, 1400, seed=3, ks=(0, 85), ms=ms, name="bwide")
 
 
-def test_bwd_adapter_gemm_wide_tiles():
-    # U = dY R^T on the 256 x 256 adapter GEMM: r 512, M 1900 (eight m tiles, the last ragged),
-    # reduction N = 33024 in 16 splits, the last one short
+def test_bwd_long_reduction_wide_rank():
+    # U = dY R^T at r 512, M 1900, over a reduction of N = 33024 on the middle path (tests/test_gpu_tile.py has the
+    # 256 x 256 adapter GEMM)
     ms = np.unique(np.concatenate([synth.stream(9, "ms").choice(1900, size=24, replace=False), np.arange(1892, 1900)]))
     _bwd_case(33024, 256, 512, 1900, seed=4, ks=(0, 1), ms=ms, name="bwd_adwide")
 
