@@ -175,14 +175,29 @@ def kernel_bytes(kernel, M, N, K, r, bwd, has_finish=True, qadapter=False):
     second = (rows * r // 2 + 2 * rows * ((r + 127) // 128)) if qadapter else 2 * r * rows
     if kernel.startswith("decode"):      # packed weight + adapter first factor + activations -> T (fp16)
         return weight + first + 2 * M * red + 2 * M * r + (0 if has_finish else 4 * M * rows)
-    if kernel.startswith(("finish", "mid_finish")):   # adapter second factor + T -> Y
+    if kernel.startswith("finish"):      # adapter second factor + T -> Y
         return second + 2 * M * r + 4 * M * rows
-    if kernel.startswith(("tile", "mid_fwd", "mid_bwd")):   # packed weight + fp16 activations + second factor + T -> Y
+    if kernel.startswith("tile"):        # packed weight + fp16 activations + second factor + T -> Y
         return weight + 2 * M * red + 2 * r * rows + 2 * M * r + 4 * M * rows
     if kernel.startswith("adapter_gemm"):  # fp16 activations + first factor -> T
         return 2 * M * red + 2 * r * red + 2 * M * r
     if kernel.startswith("rowprep"):     # activations -> their row-scaled fp16 copy
         return 4 * M * red + 4 * M
+    return 0
+
+
+def kernel_flops(kernel, M, N, K, r, bwd):
+    """Dense-equivalent FLOPs of one launch of a library kernel on one layer at M > 32: the sparse product (2MNK) and
+    the adapter's second product in the tile kernel, or with the first one in the middle path's."""
+    rows, red = (K, N) if bwd else (N, K)
+    if kernel.startswith("tile"):
+        return 2 * M * N * K + 2 * M * r * rows
+    if kernel.startswith("mid_finish"):
+        return 2 * M * r * rows
+    if kernel.startswith("mid_"):
+        return 2 * M * N * K + 2 * M * r * red
+    if kernel.startswith("adapter_gemm"):
+        return 2 * M * r * red
     return 0
 
 
@@ -389,9 +404,8 @@ def measure(wk, m, steps, warmup, dispatches, qadapter=False):
     else:
         unit = "TFLOP/s"
         value = tot_flops / (ms_per_step * 1e-3) / 1e12
-        # dominant kernel (the sparse contraction): dense-equivalent 2MNK plus the adapter's second product
-        dk_flops = sum(2 * M * pl["layer"].n * pl["layer"].k + 2 * M * pl["layer"].r *
-                       (pl["layer"].k if bwd else pl["layer"].n) for pl in per_layer) / launches_per_step
+        dk_flops = sum(kernel_flops(dominant, M, pl["layer"].n, pl["layer"].k, pl["layer"].r, bwd)
+                       for pl in per_layer) / launches_per_step
         achieved = dk_flops / avg_s / 1e12
         roofline = {"bound": "mfma", "achieved": round(achieved, 1), "peak": MFMA_F16_PEAK_TFS, "unit": "TFLOP/s",
                     "frac": round(achieved / MFMA_F16_PEAK_TFS, 4), "dense_equiv_flops_per_launch": int(dk_flops)}
