@@ -102,8 +102,8 @@ bool mid_plan(bool bwd, int64_t M, int64_t rows, int64_t red, int64_t r, int64_t
     for (int64_t s = 1; s <= 8 && (s == 1 || nch >= 4 * s); ++s) {
       const int64_t per = cdiv(nch, s), split = cdiv(nch, per), blocks = R * C * split;
       if (s > 1 && split * R * C * 2 * tc * tc * 4 + 2 * M * red > most) break;
-      // microseconds per chunk: a lone 128 x 64 block on a CU 0.40, two 0.75, a 256 x 128 block 1.15;
-      // the adapter's chain beside them takes at least about 7
+      // microseconds per chunk: a lone 128 x 64 block on a CU 0.40, two 0.75, a 256 x 128 block 1.15; the
+      // adapter's chain beside them takes at least about 7 (its units are not counted among the blocks here)
       double t = per * (tc == 64 ? (blocks <= 256 ? 0.40 : 0.75 * cdiv(blocks, 512)) : 1.15 * cdiv(blocks, 256));
       if (r > 0 && t < 7) t = 7;
       // partials written and read at about 4 TB/s

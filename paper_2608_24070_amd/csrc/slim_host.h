@@ -32,7 +32,7 @@ struct SlimPlan {
   int64_t ad_slice = 0;               // reduction length per split
   int ad_sub = 1;                      // small M: SLIM_DECODE_AD_SLICE slices per adapter wave
   int64_t ad_jblocks = 0;             // small-M path: 16-wide blocks of the adapter rank
-  // middle path (mid_gemm.hip): 128 x 64 sparse tiles over slices of the reduction
+  // middle path (mid_gemm.hip): 128 x 64 or 256 x 128 sparse tiles over slices of the reduction
   bool mid = false;
   // sparse contraction
   bool decode = false;                // small-M kernel (16-column MFMA tiles, split reduction)
@@ -40,7 +40,7 @@ struct SlimPlan {
   int dec_g = 1;                      // quantisation groups per lane group in a small-M sparse unit
   int sp_rows_tile = 0, sp_cols_tile = 0;  // output tile (rows of W or W^T, columns = M)
   int64_t sp_row_tiles = 0, sp_col_tiles = 0;
-  int sp_split = 1;                   // reduction splits (small-M kernel only)
+  int sp_split = 1;                   // reduction splits (small M and the middle path)
   int dec_units = 1;                  // small M: row tiles per sparse block
   int64_t sp_blocks = 0;              // small M: sparse blocks
   int64_t sp_chunks_per_split = 0;    // 128-wide chunks per split

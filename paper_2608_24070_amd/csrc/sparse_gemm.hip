@@ -319,8 +319,8 @@ SLIM_DEV void decode_sparse_range(const LayerArgs& a, int s, int64_t rt0, int64_
 // the reduction is long, so that there are at most about 8 splits), reading both operands straight
 // from global memory as the MFMA takes them, 64 bytes of each row at a time. With 4-bit factors that would be
 // 16 bytes of each row, eight visits to a line: the slice's 16 rows of 64 bytes come in one load there, and the
-// activations as whole rows of 256 bytes, both turned in LDS (16 x 5120 x 13824, rank 512: 20.6 -> 19.65
-// us; fp16 factors were 1 to 2 % slower turned than straight: 1 x 28672 x 8192 33.1 -> 33.65).
+// activations as whole rows of 256 bytes, both turned in LDS (the call 16 x 5120 x 13824, rank 512: 19.1 ->
+// 17.8 us; fp16 factors were 1 to 2 % slower turned than straight: 1 x 28672 x 8192 33.1 -> 33.65).
 // The four parts are added in LDS in part order, and the last unit of a column block to finish
 // sums the units' partials in split order. The partial a unit hands over is one 16 x 16
 // fragment per 16 activation rows (1 KB), which keeps the last unit's loads few.

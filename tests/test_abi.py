@@ -253,45 +253,3 @@ def test_hybrid_splits_are_as_accurate_as_the_most_considered():
         assert cps <= cps0 or 13 * cps + s // 16 + 8 <= 13 * cps0 + s0, (m, n, k, s, s0)
         fewer += s < s0
     assert fewer > 100
-
-
-def _kernel_metadata(path):
-    """{kernel symbol: its metadata} of every gfx950 code object in a library: the offload bundles' ELF files, whose
-    AMDGPU note (type 32) holds the compiler's record of each kernel as MessagePack."""
-    import struct
-
-    import msgpack
-    data = open(path, "rb").read()
-    magic, out, at = b"__CLANG_OFFLOAD_BUNDLE__", {}, 0
-    while (at := data.find(magic, at)) >= 0:
-        entry = at + len(magic) + 8
-        for _ in range(struct.unpack_from("<Q", data, entry - 8)[0]):
-            off, size, n = struct.unpack_from("<QQQ", data, entry)
-            entry += 24 + n
-            elf = data[at + off:at + off + size]
-            if elf[:4] != b"\x7fELF":
-                continue
-            shoff = struct.unpack_from("<Q", elf, 40)[0]
-            shentsize, shnum = struct.unpack_from("<HH", elf, 58)
-            for i in range(shnum):
-                typ, _, _, start, length = struct.unpack_from("<IQQQQ", elf, shoff + i * shentsize + 4)
-                if typ != 7:                                      # SHT_NOTE
-                    continue
-                p = start
-                while p < start + length:
-                    namesz, descsz, ntype = struct.unpack_from("<III", elf, p)
-                    desc = p + 12 + (namesz + 3) // 4 * 4
-                    if ntype == 32:
-                        for k in msgpack.unpackb(elf[desc:desc + descsz])["amdhsa.kernels"]:
-                            out[k[".name"]] = k
-                    p = desc + (descsz + 3) // 4 * 4
-        at += len(magic)
-    return out
-
-
-def test_kernels_keep_their_registers():
-    # a spilled register is reloaded behind a wait for every load in flight, which a pipelined loop cannot afford
-    kernels = _kernel_metadata(slim.LIB_PATH)
-    assert sum("6k_tileI" in n for n in kernels) == 4 and sum("5k_midI" in n for n in kernels) == 4
-    spilled = {n: k[".vgpr_spill_count"] for n, k in kernels.items() if k[".vgpr_spill_count"] or k[".sgpr_spill_count"]}
-    assert not spilled, spilled
