@@ -128,9 +128,11 @@ struct HybridArgs {
   int64_t M, N, K;
   int64_t payload_bytes;
   int chunks_per_split;
+  int chunks_per_sum;  // chunks that one accumulator sums before they are added to the others'
 };
 
-// One block per CU: 144 KiB of ring.
+// One block per CU: 144 KiB of ring. CARRY: a split's sum is made of several (chunks_per_sum).
+template <bool CARRY>
 __global__ void __launch_bounds__(kHGemmThreads, 1)
 k_hybrid_gemm(HybridArgs g) {
   // one variable per stage, selected by compile-time indices
@@ -219,13 +221,27 @@ k_hybrid_gemm(HybridArgs g) {
                                                (uint32_t)(sc * kHStageK * 2), 0, 0);
   };
 
-  f16_t acc[2][2];
+  // the sum of chunks_per_sum chunks, and that of the sums before it
+  f16_t acc[2][2], tot[CARRY ? 2 : 1][CARRY ? 2 : 1];
 #pragma unroll
   for (int fn = 0; fn < 2; ++fn)
 #pragma unroll
     for (int fm = 0; fm < 2; ++fm)
 #pragma unroll
-      for (int e = 0; e < 16; ++e) acc[fn][fm][e] = 0.f;
+      for (int e = 0; e < 16; ++e) {
+        acc[fn][fm][e] = 0.f;
+        if (CARRY) tot[fn][fm][e] = 0.f;
+      }
+  [[maybe_unused]] auto carry = [&]() {
+#pragma unroll
+    for (int fn = 0; fn < 2; ++fn)
+#pragma unroll
+      for (int fm = 0; fm < 2; ++fm) {
+        tot[fn][fm] += acc[fn][fm];
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[fn][fm][e] = 0.f;
+      }
+  };
 
   // The compute phase reads LDS with ds_read instructions written out, and waits for them itself:
   // the compiler cannot tell which ring slot a direct load writes, so for reads it can see it would
@@ -256,29 +272,31 @@ k_hybrid_gemm(HybridArgs g) {
                  : "+v"(o.a[0]), "+v"(o.a[1]), "+v"(o.b[0]), "+v"(o.b[1]), "+v"(o.b[2]), "+v"(o.b[3]), "+v"(o.i[0]),
                    "+v"(o.i[1]));
   };
-  // per-lane LDS byte offsets inside a stage (rows of this lane's fragments)
+  // per-lane LDS byte offsets inside a stage (rows of this lane's fragments) of the first read; read t's 16-byte slot
+  // is the first one's with 2 t (dense, activations of a 2:4 step 4 t and 4 t + 2) in its upper bits
   uint32_t ra_d[2], ra_s[2], ri_s[2], rx_[2];
-  int rsw[2], xsw[2], rsw_s[2];
 #pragma unroll
   for (int f = 0; f < 2; ++f) {
     const int r = 64 * (wn & 1) + 32 * f + l32, m = 64 * wm + 32 * f + l32;   // r: row within the tile row
-    ra_d[f] = 16384u * (uint32_t)tr + (uint32_t)r * 128u;
-    ra_s[f] = 16384u * (uint32_t)tr + (uint32_t)r * 64u;
-    ri_s[f] = 16384u * (uint32_t)tr + 8192u + (uint32_t)r * 8u;
-    rx_[f] = 32768u + (uint32_t)m * 128u;
-    rsw[f] = r & 7;
-    rsw_s[f] = (r >> 2) & 1;
-    xsw[f] = m & 7;
+    ra_d[f] = 16384u * (uint32_t)tr + (uint32_t)r * 128u + 16u * (uint32_t)(h ^ (r & 7));
+    ra_s[f] = 16384u * (uint32_t)tr + (uint32_t)r * 64u + 16u * (uint32_t)(h ^ ((r >> 2) & 1));
+    ri_s[f] = 16384u * (uint32_t)tr + 8192u + (uint32_t)r * 8u + 2u * (uint32_t)h;
+    rx_[f] = 32768u + (uint32_t)m * 128u + 16u * (uint32_t)(h ^ (m & 7));
   }
 
   auto compute = [&](auto zc, bool sparse) {
     const uint32_t base = (uint32_t)(uintptr_t)(lds_ptr_t)&ring(zc).a[0];   // the stage (a, then x)
+    // opaque in place, so that no stage's addresses are kept across the loop: they would take the second
+    // accumulators' registers
+    if constexpr (CARRY)
+      asm volatile("" : "+v"(ra_d[0]), "+v"(ra_d[1]), "+v"(ra_s[0]), "+v"(ra_s[1]), "+v"(ri_s[0]), "+v"(ri_s[1]),
+                        "+v"(rx_[0]), "+v"(rx_[1]));
     if (!sparse) {
       auto read = [&](int t, DenseOps& o) {
 #pragma unroll
         for (int f = 0; f < 2; ++f) {
-          o.a[f] = rd16(base + ra_d[f] + ((uint32_t)((2 * t + h) ^ rsw[f]) << 4));
-          o.b[f] = rd16(base + rx_[f] + ((uint32_t)((2 * t + h) ^ xsw[f]) << 4));
+          o.a[f] = rd16((ra_d[f] ^ (32u * t)) + base);
+          o.b[f] = rd16((rx_[f] ^ (32u * t)) + base);
         }
       };
       DenseOps o[2];
@@ -300,10 +318,10 @@ k_hybrid_gemm(HybridArgs g) {
 #pragma unroll
         for (int f = 0; f < 2; ++f) {
           // lane group h holds the 16 positions 32 t + 16 h .. + 15 of its row
-          o.a[f] = rd16(base + ra_s[f] + ((uint32_t)((2 * t + h) ^ rsw_s[f]) << 4));
-          o.i[f] = rd_u16(base + ri_s[f] + 2u * (uint32_t)(2 * t + h));
-          o.b[2 * f] = rd16(base + rx_[f] + ((uint32_t)((4 * t + h) ^ xsw[f]) << 4));
-          o.b[2 * f + 1] = rd16(base + rx_[f] + ((uint32_t)((4 * t + 2 + h) ^ xsw[f]) << 4));
+          o.a[f] = rd16((ra_s[f] ^ (32u * t)) + base);
+          o.i[f] = rd_u16(ri_s[f] + 4u * t + base);
+          o.b[2 * f] = rd16((rx_[f] ^ (64u * t)) + base);
+          o.b[2 * f + 1] = rd16((rx_[f] ^ (64u * t + 32u)) + base);
         }
       };
       SparseOps o[2];
@@ -335,6 +353,7 @@ k_hybrid_gemm(HybridArgs g) {
       default: __builtin_amdgcn_s_waitcnt(vmcnt_lgkm0_wait(6)); break;
     }
   };
+  [[maybe_unused]] int left = 2 * g.chunks_per_sum;      // stages until the next carry
   auto step = [&](int64_t s, auto zc) {
     constexpr int z = decltype(zc)::value;
     const int ahead = loads_of(s + 1);
@@ -344,6 +363,11 @@ k_hybrid_gemm(HybridArgs g) {
     __builtin_amdgcn_sched_barrier(0);
     issue(s + 2, std::integral_constant<int, (z + 2) % kHRing>{});
     compute(zc, (kind_of(tr, s) & kHSparseBit) != 0);
+    if constexpr (CARRY)
+      if (--left == 0) {
+        carry();
+        left = 2 * g.chunks_per_sum;
+      }
   };
 
   if (s_begin < s_end) {
@@ -358,6 +382,8 @@ k_hybrid_gemm(HybridArgs g) {
     __builtin_amdgcn_s_waitcnt(0);
   }
 
+  if constexpr (CARRY) carry();
+
   // D[i][j] of a 32x32 fragment: lane j + 32 ((i / 4) % 2), element 4 (i / 8) + i % 4
   float* out = g.out + (int64_t)blockIdx.z * g.M * g.N;
 #pragma unroll
@@ -370,8 +396,8 @@ k_hybrid_gemm(HybridArgs g) {
       for (int q = 0; q < 4; ++q) {
         const int64_t nn = n0 + 64 * wn + 32 * fn + 8 * q + 4 * h;
         if (nn >= g.N) continue;
-        const f4_t o = {acc[fn][fm][4 * q], acc[fn][fm][4 * q + 1], acc[fn][fm][4 * q + 2], acc[fn][fm][4 * q + 3]};
-        *reinterpret_cast<f4_t*>(out + m * g.N + nn) = o;
+        const f16_t& v = CARRY ? tot[CARRY ? fn : 0][CARRY ? fm : 0] : acc[fn][fm];
+        *reinterpret_cast<f4_t*>(out + m * g.N + nn) = f4_t{v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]};
       }
   }
 }
@@ -530,32 +556,25 @@ k_hybrid_few(HybridArgs g) {
   }
 }
 
-// Sums of the split partials, in an order fixed by the sizes: 256 / G outputs (of four values) per block, the splits
-// over G groups of threads with four loads in flight each, the groups' sums added through LDS. One thread per output
-// walking all splits waited for every load in turn (112 splits: 28 us).
-template <int G>
+// Sums of the split partials, in an order fixed by the split count: 64 outputs (of four values) per block, the
+// splits over four groups of threads with four loads in flight each, the groups' sums added through LDS. One
+// thread per output walking all splits waited for every load in turn (112 splits: 28 us).
 __global__ void __launch_bounds__(kHThreads)
 k_hybrid_reduce(const float* __restrict__ part, int splits, int64_t count4, float* __restrict__ Y) {
-  constexpr int kOut = kHThreads / G;
-  __shared__ f4_t sums[G > 1 ? G - 1 : 1][kOut];
-  const int at = threadIdx.x % kOut, grp = threadIdx.x / kOut;
-  const int64_t i = (int64_t)blockIdx.x * kOut + at;
+  __shared__ f4_t sums[3][64];
+  const int lane = threadIdx.x & 63, grp = threadIdx.x >> 6;
+  const int64_t i = (int64_t)blockIdx.x * 64 + lane;
   const f4_t* p = reinterpret_cast<const f4_t*>(part) + (i < count4 ? i : count4 - 1);
   f4_t s = f4_t{0.f, 0.f, 0.f, 0.f};
   int z = grp;
-  for (; z + 3 * G < splits; z += 4 * G) {
-    const f4_t v0 = p[z * count4], v1 = p[(z + G) * count4], v2 = p[(z + 2 * G) * count4], v3 = p[(z + 3 * G) * count4];
+  for (; z + 12 < splits; z += 16) {
+    const f4_t v0 = p[z * count4], v1 = p[(z + 4) * count4], v2 = p[(z + 8) * count4], v3 = p[(z + 12) * count4];
     s += (v0 + v1) + (v2 + v3);
   }
-  for (; z < splits; z += G) s += p[z * count4];
-  if constexpr (G > 1) {
-    if (grp > 0) sums[grp - 1][at] = s;
-    __syncthreads();
-    if (grp > 0) return;
-    static_assert(G == 4, "the groups' sums are added two by two");
-    s = (s + sums[0][at]) + (sums[1][at] + sums[2][at]);
-  }
-  if (i < count4) reinterpret_cast<f4_t*>(Y)[i] = s;
+  for (; z < splits; z += 4) s += p[z * count4];
+  if (grp > 0) sums[grp - 1][lane] = s;
+  __syncthreads();
+  if (grp == 0 && i < count4) reinterpret_cast<f4_t*>(Y)[i] = (s + sums[0][lane]) + (sums[1][lane] + sums[2][lane]);
 }
 
 // Rows served by k_hybrid_few. Its weights are read once whatever M is, and X once per row block, so it is the
@@ -573,19 +592,21 @@ bool hybrid_few(int64_t M, int64_t N, int64_t K) {
 
 struct HybridPlan {
   bool few;
-  int64_t tiles, splits, chunks_per_split;
+  int64_t tiles, splits, chunks_per_split, chunks_per_sum;
   size_t ws;
 };
 
-// Splits of K: the count of least estimated time of those that sum as accurately as the most that are considered, s0
-// (no more than two rounds of blocks), added up one after another. A split's sum makes up to eight roundings per
-// chunk, each about 1.6 times (in variance, measured) as heavy as an addition of the partials, of which the
-// reduction's order leaves at most about s / 16 + 8 in a chain: 13 chunks + s / 16 + 8 <= 13 chunks0 + s0. With the time
-// alone 64 x 14336 x 14336 took four splits instead of ten, 80 us instead of 92 and 3.3e-7 from 64 bits instead
-// of 2.2e-7. A block takes t0 = 4.5 us and 2 us per chunk (fitted at 64
+// Splits of K: the count of least estimated time. A block takes t0 = 4.5 us and 2 us per chunk (fitted at 64
 // rows of 4096 x 4096 in 1 to 32 splits, 65 to 13 us a launch; with 256 blocks at work a chunk's 45 KB each
 // make 5.8 TB/s), blocks run 256 at a time with the last split's shorter ones last, and the partials cost
 // the reduction's launch, 3 us, and their writing and reading at 7 TB/s.
+// Fewer splits sum more of K each. One accumulator for all of it rounds worse than the most splits that are
+// considered, s0 (no more than two rounds of blocks): 64 x 14336 x 14336 in four splits instead of ten was 3.3e-7 from
+// 64 bits instead of 2.2e-7. So a split adds up sums of chunks_per_sum chunks, as many as leave the rounding no larger
+// than s0's added one after another: a sum makes up to eight roundings per chunk, each about 1.6 times (in variance,
+// measured) as heavy as an addition, of which the reduction's order leaves at most about s / 16 + 8 in a chain. That
+// costs 2 to 6 % of the call (64 x 14336 x 14336: 79 -> 84 us, 93 in ten splits; 383 x 2688 x 640, five chunks in all,
+// 16.6 -> 18.3).
 HybridPlan hybrid_plan(int64_t M, int64_t N, int64_t K) {
   HybridPlan p{};
   p.few = hybrid_few(M, N, K);
@@ -603,7 +624,6 @@ HybridPlan hybrid_plan(int64_t M, int64_t N, int64_t K) {
   for (uint32_t s = 1; s <= (uint32_t)most; ++s) {
     const uint32_t cps = (nch + s - 1) / s;
     if (cps * (s - 1) >= nch) continue;                 // fewer splits of as many chunks
-    if (cps > cps0 && 13 * cps + s / 16 + 8 > 13 * cps0 + s0) continue;
     const double full = 4.5 + 2.0 * cps, last = 4.5 + 2.0 * (nch - (s - 1) * cps);
     const int64_t nfull = p.tiles * (s - 1), busy = nfull % 256, idle = 256 - busy;
     // whole rounds, then the busy blocks' end or the last split's, in as many rounds as the idle CUs need
@@ -615,6 +635,9 @@ HybridPlan hybrid_plan(int64_t M, int64_t N, int64_t K) {
       best = t;
       p.splits = s;
       p.chunks_per_split = cps;
+      uint32_t sum = cps;
+      while (sum > cps0 && 13 * sum + (cps + sum - 1) / sum - 1 + s / 16 + 8 > 13 * cps0 + s0) --sum;
+      p.chunks_per_sum = sum;
     }
   }
   p.ws = p.splits > 1 ? (size_t)p.splits * M * N * sizeof(float) : 0;
@@ -705,7 +728,7 @@ extern "C" int slim_linear_hybrid(const void* X, int64_t M, int64_t N, int64_t K
   if (p.splits > 1 && !slim_aligned16(ws)) return SLIM_EALIGN;
   hipStream_t s = (hipStream_t)stream;
   if (p.few) {
-    const HybridArgs a{static_cast<const uint16_t*>(X), tile_info, payload, Y, M, N, K, (int64_t)payload_bytes, 0};
+    const HybridArgs a{static_cast<const uint16_t*>(X), tile_info, payload, Y, M, N, K, (int64_t)payload_bytes, 0, 0};
     SlimKernelTimer timer("hybrid_few", s);
     const int64_t cols = (M + 31) / 32;
     auto go = [&](auto kernel, int rows, int waves) {
@@ -727,24 +750,19 @@ extern "C" int slim_linear_hybrid(const void* X, int64_t M, int64_t N, int64_t K
     return hipGetLastError() == hipSuccess ? SLIM_OK : SLIM_EDEVICE;
   }
   HybridArgs a{static_cast<const uint16_t*>(X), tile_info, payload, p.splits > 1 ? static_cast<float*>(ws) : Y,
-               M, N, K, (int64_t)payload_bytes, (int)p.chunks_per_split};
+               M, N, K, (int64_t)payload_bytes, (int)p.chunks_per_split, (int)p.chunks_per_sum};
   {
     SlimKernelTimer timer("hybrid_gemm", s);
-    SLIM_LAUNCH(timer, k_hybrid_gemm, dim3((unsigned)((N + kHRows - 1) / kHRows), (unsigned)((M + kHT - 1) / kHT),
-                                           (unsigned)p.splits),
+    auto kernel = p.chunks_per_split > p.chunks_per_sum ? k_hybrid_gemm<true> : k_hybrid_gemm<false>;
+    SLIM_LAUNCH(timer, kernel, dim3((unsigned)((N + kHRows - 1) / kHRows), (unsigned)((M + kHT - 1) / kHT),
+                                    (unsigned)p.splits),
                 dim3(kHGemmThreads), s, a);
   }
   if (p.splits > 1) {
     const int64_t count4 = M * N / 4;
     SlimKernelTimer timer("hybrid_reduce", s);
-    auto reduce = [&](auto kernel, int64_t outs) {
-      SLIM_LAUNCH(timer, kernel, dim3((unsigned)((count4 + outs - 1) / outs)), dim3(kHThreads), s,
-                  (const float*)static_cast<float*>(ws), (int)p.splits, count4, Y);
-    };
-    // from 512 blocks of one thread per output on, four threads for each only add blocks (128 x 8192 x 2048, 16
-    // splits: 36.2 us against 39.0; below it 120 x 512 x 14336: 21.7 against 18.5)
-    if (count4 >= 512 * kHThreads) reduce(k_hybrid_reduce<1>, kHThreads);
-    else reduce(k_hybrid_reduce<4>, kHThreads / 4);
+    SLIM_LAUNCH(timer, k_hybrid_reduce, dim3((unsigned)((count4 + 63) / 64)), dim3(kHThreads), s,
+                (const float*)static_cast<float*>(ws), (int)p.splits, count4, Y);
   }
   return hipGetLastError() == hipSuccess ? SLIM_OK : SLIM_EDEVICE;
 }

@@ -95,7 +95,7 @@ def test_written_out_reads_land_before_their_registers_are_used(tmp_path):
     bodies = code_objects.disassembly(slim.LIB_PATH, str(tmp_path))
     names = [n for n in bodies if re.search(r"\d(k_tileI|k_midI|k_adapter_tn|k_hybrid_gemm|k_grad_w|k_grad_w_smallI)", n)
              and not n.endswith(".kd")]
-    assert len(names) == 4 + 4 + 1 + 1 + 2 + 2, names
+    assert len(names) == 4 + 4 + 1 + 2 + 2 + 2, names
     for n in names:
         assert sum(t.startswith("ds_read") for _, t in bodies[n]) > 16, n
         assert not touched_in_flight(bodies[n]), n

@@ -134,7 +134,8 @@ def _split_chain_error(X, W, tiles):
 # Long sums stay as accurate as K cut for 512 blocks: the kernel for few rows (both of its shapes for more than 16
 # rows) and the GEMM. 1.15: the matrix instructions' own order of their terms, and the sample.
 @pytest.mark.parametrize("m,n,k", [(32, 4224, 14336), (32, 2176, 14336), (64, 4096, 4096), (64, 2048, 4096), (16, 4224, 14336),
-                                   (333, 5120, 5120), (100, 4096, 4096), (130, 1024, 8192)])
+                                   (333, 5120, 5120), (100, 4096, 4096), (130, 1024, 8192), (500, 2048, 14336),
+                                   (1332, 1024, 3584)])
 def test_long_sums_stay_accurate(m, n, k):
     print(f"hybrid accuracy m={m} n={n} k={k}", flush=True)
     W = _w(n, k, 9)
